@@ -20,12 +20,26 @@ SOURCES = ["bssn_api.cpp", "bssn_rhs_o4.hip", "bssn_rhs_o8.hip",
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function"]
+# The stage kernels hold a point's working set in 256 registers per lane.
+# Hoisting the stencils' and the algebra's FP64 constants out of the tile loop
+# (machine LICM) would take dozens of them and spill: off for these files.
+# The order-8 work-list kernels need the scheduler's exact register tracking
+# as well (2% slower code, so only where it takes the last spills away).
+STAGE_FLAGS = ["-mllvm", "-disable-machine-licm"]
+EXTRA_FLAGS = {
+    "bssn_rhs_o4.hip": STAGE_FLAGS,
+    "bssn_rhs_o8.hip": STAGE_FLAGS,
+    "bssn_batch_o4.hip": STAGE_FLAGS,
+    "bssn_batch_o8.hip": STAGE_FLAGS + ["-mllvm",
+                                        "-amdgpu-use-amdgpu-trackers"],
+}
 
 
 def _compile(src, verbose):
     out = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
     lang = ["-x", "hip"] if src.endswith(".cpp") else []
-    cmd = ["hipcc"] + FLAGS + lang + ["-c", os.path.join(CSRC, src), "-o",
+    extra = EXTRA_FLAGS.get(src, [])
+    cmd = ["hipcc"] + FLAGS + extra + lang + ["-c", os.path.join(CSRC, src), "-o",
                                       out]
     if verbose:
         print(" ".join(cmd), flush=True)

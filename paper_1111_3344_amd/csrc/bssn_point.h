@@ -232,28 +232,13 @@ __device__ __forceinline__ T mixed(const L& ld, int s, int a, int b, T ihab) {
   return v;
 }
 
-// Loaders that form the three mixed derivatives of a slot together (sharing
-// inner sums across the tile) declare kSharedMixed = true and mixed3().
-template <class L, class = void>
-struct SharedMixed {
-  static constexpr bool value = false;
-};
-template <class L>
-struct SharedMixed<L, decltype(void(L::kSharedMixed))> {
-  static constexpr bool value = L::kSharedMixed;
-};
-
 // d_x d_y, d_x d_z, d_y d_z of slot s at the point.
 template <int ORDER, typename T, class L>
 __device__ __forceinline__ void mixed_all(const L& ld, int s, T ihxy, T ihxz,
                                           T ihyz, T& dxy, T& dxz, T& dyz) {
-  if constexpr (SharedMixed<L>::value) {
-    ld.template mixed3<ORDER, T>(ihxy, ihxz, ihyz, dxy, dxz, dyz);
-  } else {
-    dxy = mixed<ORDER, T>(ld, s, 0, 1, ihxy);
-    dxz = mixed<ORDER, T>(ld, s, 0, 2, ihxz);
-    dyz = mixed<ORDER, T>(ld, s, 1, 2, ihyz);
-  }
+  dxy = mixed<ORDER, T>(ld, s, 0, 1, ihxy);
+  dxz = mixed<ORDER, T>(ld, s, 0, 2, ihxz);
+  dyz = mixed<ORDER, T>(ld, s, 1, 2, ihyz);
 }
 
 template <typename T>
@@ -265,6 +250,289 @@ __device__ __forceinline__ double t_exp<double>(double x) {
 template <>
 __device__ __forceinline__ float t_exp<float>(float x) {
   return expf(x);
+}
+
+// ---- the algebra, shared by the point function and the split kernels ---------
+// inverse conformal metric (adjugate / determinant)
+template <typename T>
+__device__ __forceinline__ void inverse_metric(const T (&gt)[6], T (&gu)[6]) {
+  const T c00 = gt[3] * gt[5] - gt[4] * gt[4];
+  const T c01 = gt[2] * gt[4] - gt[1] * gt[5];
+  const T c02 = gt[1] * gt[4] - gt[2] * gt[3];
+  const T idet = T(1) / (gt[0] * c00 + gt[1] * c01 + gt[2] * c02);
+  gu[0] = c00 * idet;
+  gu[1] = c01 * idet;
+  gu[2] = c02 * idet;
+  gu[3] = (gt[0] * gt[5] - gt[2] * gt[2]) * idet;
+  gu[4] = (gt[1] * gt[2] - gt[0] * gt[4]) * idet;
+  gu[5] = (gt[0] * gt[3] - gt[1] * gt[1]) * idet;
+}
+
+// advection + dissipation weights of one axis from the shift there
+template <int ORDER, typename T>
+__device__ __forceinline__ void axis_weights(double bb, double ko_eps,
+                                             double ih,
+                                             T (&cw)[2 * FD<ORDER>::R]) {
+  using F = FD<ORDER>;
+  constexpr int R = F::R;
+  const bool pos = bb > 0.0;
+#pragma unroll
+  for (int k = -R; k <= R; ++k) {
+    if (k == 0) continue;
+    const double W = pos ? F::up(k) : -F::up(-k);
+    cw[WI<R>(k)] = T((bb * W + ko_eps * F::ko(k)) * ih);
+  }
+}
+
+// -1/2 of the trace of a second derivative (R~_ij's leading term)
+template <typename T>
+__device__ __forceinline__ T ricci_trace(const T (&gu)[6], const T (&d2)[3],
+                                         T dxy, T dxz, T dyz) {
+  return T(-0.5) * (gu[0] * d2[0] + gu[3] * d2[1] + gu[5] * d2[2] +
+                    T(2) * (gu[1] * dxy + gu[2] * dxz + gu[4] * dyz));
+}
+
+// Christoffel symbols Gl[i][S(j,k)] = Gamma~_ijk, Gu[i][S(j,k)] =
+// Gamma~^i_jk, Gd^i = d_l gt^li, and the quadratic terms of R~_ij into Rt.
+template <typename T, bool FENCE = false>
+__device__ __forceinline__ void connection(const T (&dgt)[6][3],
+                                           const T (&gu)[6], T (&Gu)[3][6],
+                                           T (&Gd)[3], T (&Rt)[6]) {
+  T Gl[3][6];
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+      for (int k = j; k < 3; ++k)
+        Gl[i][S(j, k)] = T(0.5) * (dgt[S(i, j)][k] + dgt[S(i, k)][j] -
+                                   dgt[S(j, k)][i]);
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int m = 0; m < 6; ++m)
+      Gu[i][m] = gu[S(i, 0)] * Gl[0][m] + gu[S(i, 1)] * Gl[1][m] +
+                 gu[S(i, 2)] * Gl[2][m];
+  // Gd^i = d_l gt^li = -gt^ib Q_b, Q_b = gt^la d_l gt_ab
+  {
+    T Q[3];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      T s = T(0);
+#pragma unroll
+      for (int l = 0; l < 3; ++l)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) s += gu[S(l, a)] * dgt[S(a, b)][l];
+      Q[b] = s;
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      Gd[i] = -(gu[S(i, 0)] * Q[0] + gu[S(i, 1)] * Q[1] + gu[S(i, 2)] * Q[2]);
+  }
+  // quadratic Ricci terms, one k at a time:
+  //   gt^lm (G^k_li G_jkm + G^k_lj G_ikm + G^k_im G_klj)
+  //   = sum_k sum_m [ H3_k[m][i] Gl_jkm + H3_k[m][j] Gl_ikm
+  //                  + G^k_im H2_k[m][j] ]
+  // with H3_k[m][i] = gt^ml G^k_li and H2_k[m][j] = gt^ml G_klj, and
+  //   - (Gl_ijk + Gl_jik) Gd^k / 2
+  if constexpr (FENCE) {
+    // the same sums one (k, m) at a time: 6 instead of 18 products live
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+#pragma unroll
+      for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = i; j < 3; ++j)
+          Rt[S(i, j)] -= T(0.5) * (Gl[i][S(j, k)] + Gl[j][S(i, k)]) * Gd[k];
+#pragma unroll
+      for (int m = 0; m < 3; ++m) {
+        T H3[3], H2[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          H3[i] = gu[S(m, 0)] * Gu[k][S(0, i)] + gu[S(m, 1)] * Gu[k][S(1, i)] +
+                  gu[S(m, 2)] * Gu[k][S(2, i)];
+          H2[i] = gu[S(m, 0)] * Gl[k][S(0, i)] + gu[S(m, 1)] * Gl[k][S(1, i)] +
+                  gu[S(m, 2)] * Gl[k][S(2, i)];
+        }
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+          for (int j = i; j < 3; ++j) {
+            Rt[S(i, j)] += H3[i] * Gl[j][S(k, m)] + H3[j] * Gl[i][S(k, m)] +
+                           Gu[k][S(i, m)] * H2[j];
+            keep(Rt[S(i, j)]);
+          }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      T H3[3][3], H2[3][3];
+#pragma unroll
+      for (int m = 0; m < 3; ++m)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          H3[m][i] = gu[S(m, 0)] * Gu[k][S(0, i)] + gu[S(m, 1)] * Gu[k][S(1, i)] +
+                     gu[S(m, 2)] * Gu[k][S(2, i)];
+          H2[m][i] = gu[S(m, 0)] * Gl[k][S(0, i)] + gu[S(m, 1)] * Gl[k][S(1, i)] +
+                     gu[S(m, 2)] * Gl[k][S(2, i)];
+        }
+#pragma unroll
+      for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = i; j < 3; ++j) {
+          T s = -T(0.5) * (Gl[i][S(j, k)] + Gl[j][S(i, k)]) * Gd[k];
+#pragma unroll
+          for (int m = 0; m < 3; ++m)
+            s += H3[m][i] * Gl[j][S(k, m)] + H3[m][j] * Gl[i][S(k, m)] +
+                 Gu[k][S(i, m)] * H2[m][j];
+          Rt[S(i, j)] += s;
+          keep(Rt[S(i, j)]);
+        }
+    }
+  }
+}
+
+// R^phi_ij into Rt from d_i phi and d_i d_j phi
+template <typename T>
+__device__ __forceinline__ void phi_ricci(const T (&gt)[6], const T (&gu)[6],
+                                          const T (&Gu)[3][6],
+                                          const T (&dphi)[3],
+                                          const T (&dd)[6], T (&Rt)[6]) {
+  T DD[6];
+#pragma unroll
+  for (int m = 0; m < 6; ++m)
+    DD[m] = dd[m] - (Gu[0][m] * dphi[0] + Gu[1][m] * dphi[1] +
+                     Gu[2][m] * dphi[2]);
+  const T trDD = gu[0] * DD[0] + gu[3] * DD[3] + gu[5] * DD[5] +
+                 T(2) * (gu[1] * DD[1] + gu[2] * DD[2] + gu[4] * DD[4]);
+  const T dphi2 =
+      gu[0] * dphi[0] * dphi[0] + gu[3] * dphi[1] * dphi[1] +
+      gu[5] * dphi[2] * dphi[2] +
+      T(2) * (gu[1] * dphi[0] * dphi[1] + gu[2] * dphi[0] * dphi[2] +
+              gu[4] * dphi[1] * dphi[2]);
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = i; j < 3; ++j) {
+      const int m = S(i, j);
+      Rt[m] += T(-2) * DD[m] - T(2) * gt[m] * trDD +
+               T(4) * dphi[i] * dphi[j] - T(4) * gt[m] * dphi2;
+    }
+}
+
+// Scheduling fence between blocks of algebra (FENCE: the split kernels,
+// where overlapping the blocks would exceed the registers).
+template <bool FENCE>
+__device__ __forceinline__ void algebra_fence() {
+  if constexpr (FENCE) __builtin_amdgcn_sched_barrier(0);
+}
+
+// The lapse's terms: the A~_ij and K sources into rA and rK, and the lapse
+// part of Gt's source into Tg.
+template <typename T, bool FENCE = false>
+__device__ __forceinline__ void lapse_terms(
+    const T (&gt)[6], const T (&gu)[6], const T (&Gu)[3][6],
+    const T (&At)[6], const T (&Rt)[6], T em4phi, const T (&dphi)[3], T trK,
+    T alpha, const T (&dalp)[3], const T (&dd)[6], T (&rA)[6], T& rK,
+    T (&Tg)[3]) {
+  // X_ij = alpha R_ij - D_i D_j alpha + 2 (d_i phi d_j alpha + ...)
+  {
+    T DD[6], X[6];
+#pragma unroll
+    for (int m = 0; m < 6; ++m)
+      DD[m] = dd[m] - (Gu[0][m] * dalp[0] + Gu[1][m] * dalp[1] +
+                       Gu[2][m] * dalp[2]);
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int j = i; j < 3; ++j) {
+        const int m = S(i, j);
+        X[m] = alpha * Rt[m] - DD[m] +
+               T(2) * (dphi[i] * dalp[j] + dphi[j] * dalp[i]);
+      }
+    const T trX = gu[0] * X[0] + gu[3] * X[3] + gu[5] * X[5] +
+                  T(2) * (gu[1] * X[1] + gu[2] * X[2] + gu[4] * X[4]);
+#pragma unroll
+    for (int m = 0; m < 6; ++m) {
+      rA[m] += em4phi * (X[m] - gt[m] * trX * T(1.0 / 3.0)) +
+               alpha * trK * At[m];
+      if (FENCE) keep(rA[m]);
+    }
+    const T trDD = gu[0] * DD[0] + gu[3] * DD[3] + gu[5] * DD[5] +
+                   T(2) * (gu[1] * DD[1] + gu[2] * DD[2] + gu[4] * DD[4]);
+    const T dpda =
+        gu[0] * dphi[0] * dalp[0] + gu[3] * dphi[1] * dalp[1] +
+        gu[5] * dphi[2] * dalp[2] +
+        gu[1] * (dphi[0] * dalp[1] + dphi[1] * dalp[0]) +
+        gu[2] * (dphi[0] * dalp[2] + dphi[2] * dalp[0]) +
+        gu[4] * (dphi[1] * dalp[2] + dphi[2] * dalp[1]);
+    rK += -em4phi * (trDD + T(2) * dpda) + alpha * (trK * trK * T(1.0 / 3.0));
+    if (FENCE) keep(rK);
+  }
+  algebra_fence<FENCE>();
+  // A~^i_j, A~^ij and A~_ij A~^ij
+  T Auu[6];
+  {
+    T Aud[3][3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+        Aud[i][j] = gu[S(i, 0)] * At[S(0, j)] + gu[S(i, 1)] * At[S(1, j)] +
+                    gu[S(i, 2)] * At[S(2, j)];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int j = i; j < 3; ++j)
+        Auu[S(i, j)] = Aud[i][0] * gu[S(0, j)] + Aud[i][1] * gu[S(1, j)] +
+                       Aud[i][2] * gu[S(2, j)];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int j = i; j < 3; ++j)
+        rA[S(i, j)] -= T(2) * alpha *
+                       (At[S(i, 0)] * Aud[0][j] + At[S(i, 1)] * Aud[1][j] +
+                        At[S(i, 2)] * Aud[2][j]);
+  }
+  const T AA = At[0] * Auu[0] + At[3] * Auu[3] + At[5] * Auu[5] +
+               T(2) * (At[1] * Auu[1] + At[2] * Auu[2] + At[4] * Auu[4]);
+  rK += alpha * AA;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const T GA = Gu[i][0] * Auu[0] + Gu[i][3] * Auu[3] + Gu[i][5] * Auu[5] +
+                 T(2) * (Gu[i][1] * Auu[1] + Gu[i][2] * Auu[2] +
+                         Gu[i][4] * Auu[4]);
+    const T Ad = Auu[S(i, 0)] * dalp[0] + Auu[S(i, 1)] * dalp[1] +
+                 Auu[S(i, 2)] * dalp[2];
+    const T Ap = Auu[S(i, 0)] * dphi[0] + Auu[S(i, 1)] * dphi[1] +
+                 Auu[S(i, 2)] * dphi[2];
+    Tg[i] += T(-2) * Ad + T(2) * alpha * (GA + T(6) * Ap);
+  }
+}
+
+// The terms of shift component k: the shift parts of the gt_ij and A~_ij
+// sources into rg and rA, of Gt's source into Tg; V_j = d_j d_k beta^k and
+// div beta are gathered over the components.
+template <typename T>
+__device__ __forceinline__ void shift_terms(
+    int k, const T (&gt)[6], const T (&gu)[6], const T (&At)[6],
+    const T (&Gd)[3], const T (&db)[3], const T (&dd)[6], T (&rg)[6],
+    T (&rA)[6], T (&Tg)[3], T (&V)[3], T& divb) {
+  Tg[k] += gu[0] * dd[0] + gu[3] * dd[3] + gu[5] * dd[5] +
+           T(2) * (gu[1] * dd[1] + gu[2] * dd[2] + gu[4] * dd[4]);
+  Tg[k] += Gd[0] * db[0] + Gd[1] * db[1] + Gd[2] * db[2];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) V[j] += dd[S(j, k)];
+  divb += db[k];
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = i; j < 3; ++j) {
+      rg[S(i, j)] += gt[S(k, i)] * db[j] + gt[S(k, j)] * db[i];
+      rA[S(i, j)] += At[S(k, i)] * db[j] + At[S(k, j)] * db[i];
+    }
 }
 
 // ---- the right-hand side at one point --------------------------------------------
@@ -294,32 +562,14 @@ __device__ __forceinline__ void point_rhs(const L& ld, const Sp& sp,
   for (int m = 0; m < 6; ++m) gt[m] = T(ld.g(GXX + m));
   const T alpha = T(ld.g(ALP));
 
-  // inverse conformal metric (adjugate / determinant)
-  const T c00 = gt[3] * gt[5] - gt[4] * gt[4];
-  const T c01 = gt[2] * gt[4] - gt[1] * gt[5];
-  const T c02 = gt[1] * gt[4] - gt[2] * gt[3];
-  const T idet = T(1) / (gt[0] * c00 + gt[1] * c01 + gt[2] * c02);
   T gu[6];
-  gu[0] = c00 * idet;
-  gu[1] = c01 * idet;
-  gu[2] = c02 * idet;
-  gu[3] = (gt[0] * gt[5] - gt[2] * gt[2]) * idet;
-  gu[4] = (gt[1] * gt[2] - gt[0] * gt[4]) * idet;
-  gu[5] = (gt[0] * gt[3] - gt[1] * gt[1]) * idet;
+  inverse_metric<T>(gt, gu);
 
   // advection + dissipation weights per axis
   T cw[3][2 * R];
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    const double bb = ld.g(BETX + a);
-    const bool pos = bb > 0.0;
-#pragma unroll
-    for (int k = -R; k <= R; ++k) {
-      if (k == 0) continue;
-      const double W = pos ? F::up(k) : -F::up(-k);
-      cw[a][WI<R>(k)] = T((bb * W + G.ko_eps * F::ko(k)) * sp.ih[a]);
-    }
-  }
+  for (int a = 0; a < 3; ++a)
+    axis_weights<ORDER, T>(ld.g(BETX + a), G.ko_eps, sp.ih[a], cw[a]);
 
   // ---- gt_ij (first derivatives; trace of the second derivatives into
   //      R~), alternating with A~_ij (advection only; centre value kept) --
@@ -335,8 +585,7 @@ __device__ __forceinline__ void point_rhs(const L& ld, const Sp& sp,
     BSSN_PHASE();
     T dxy, dxz, dyz;
     mixed_all<ORDER, T>(ld, GXX + m, ihxy, ihxz, ihyz, dxy, dxz, dyz);
-    Rt[m] = T(-0.5) * (gu[0] * d2[0] + gu[3] * d2[1] + gu[5] * d2[2] +
-                       T(2) * (gu[1] * dxy + gu[2] * dxz + gu[4] * dyz));
+    Rt[m] = ricci_trace<T>(gu, d2, dxy, dxz, dyz);
     keep(Rt[m]);
     ld.enter(AXX + m);
     At[m] = T(ld.c(AXX + m));
@@ -344,71 +593,8 @@ __device__ __forceinline__ void point_rhs(const L& ld, const Sp& sp,
                                               nullptr, nullptr);
   }
 
-  // Christoffel symbols: Gl[i][S(j,k)] = Gamma~_ijk, Gu[i][S(j,k)] =
-  // Gamma~^i_jk
-  T Gl[3][6], Gu[3][6];
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-#pragma unroll
-      for (int k = j; k < 3; ++k)
-        Gl[i][S(j, k)] = T(0.5) * (dgt[S(i, j)][k] + dgt[S(i, k)][j] -
-                                   dgt[S(j, k)][i]);
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int m = 0; m < 6; ++m)
-      Gu[i][m] = gu[S(i, 0)] * Gl[0][m] + gu[S(i, 1)] * Gl[1][m] +
-                 gu[S(i, 2)] * Gl[2][m];
-  // Gd^i = d_l gt^li = -gt^ib Q_b, Q_b = gt^la d_l gt_ab
-  T Gd[3];
-  {
-    T Q[3];
-#pragma unroll
-    for (int b = 0; b < 3; ++b) {
-      T s = T(0);
-#pragma unroll
-      for (int l = 0; l < 3; ++l)
-#pragma unroll
-        for (int a = 0; a < 3; ++a) s += gu[S(l, a)] * dgt[S(a, b)][l];
-      Q[b] = s;
-    }
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-      Gd[i] = -(gu[S(i, 0)] * Q[0] + gu[S(i, 1)] * Q[1] + gu[S(i, 2)] * Q[2]);
-  }
-  // quadratic Ricci terms, one k at a time:
-  //   gt^lm (G^k_li G_jkm + G^k_lj G_ikm + G^k_im G_klj)
-  //   = sum_k sum_m [ H3_k[m][i] Gl_jkm + H3_k[m][j] Gl_ikm
-  //                  + G^k_im H2_k[m][j] ]
-  // with H3_k[m][i] = gt^ml G^k_li and H2_k[m][j] = gt^ml G_klj, and
-  //   - (Gl_ijk + Gl_jik) Gd^k / 2
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    T H3[3][3], H2[3][3];
-#pragma unroll
-    for (int m = 0; m < 3; ++m)
-#pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        H3[m][i] = gu[S(m, 0)] * Gu[k][S(0, i)] + gu[S(m, 1)] * Gu[k][S(1, i)] +
-                   gu[S(m, 2)] * Gu[k][S(2, i)];
-        H2[m][i] = gu[S(m, 0)] * Gl[k][S(0, i)] + gu[S(m, 1)] * Gl[k][S(1, i)] +
-                   gu[S(m, 2)] * Gl[k][S(2, i)];
-      }
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-      for (int j = i; j < 3; ++j) {
-        T s = -T(0.5) * (Gl[i][S(j, k)] + Gl[j][S(i, k)]) * Gd[k];
-#pragma unroll
-        for (int m = 0; m < 3; ++m)
-          s += H3[m][i] * Gl[j][S(k, m)] + H3[m][j] * Gl[i][S(k, m)] +
-               Gu[k][S(i, m)] * H2[m][j];
-        Rt[S(i, j)] += s;
-        keep(Rt[S(i, j)]);
-      }
-  }
+  T Gu[3][6], Gd[3];
+  connection<T>(dgt, gu, Gu, Gd, Rt);
 
   // ---- Gt^k (d_j Gt^k into R~_ij), alternating with B^k --------------------
   T Bv[3];
@@ -442,26 +628,7 @@ __device__ __forceinline__ void point_rhs(const L& ld, const Sp& sp,
     dd[5] = d2[2];
     BSSN_PHASE();
     mixed_all<ORDER, T>(ld, PHI, ihxy, ihxz, ihyz, dd[1], dd[2], dd[4]);
-    T DD[6];
-#pragma unroll
-    for (int m = 0; m < 6; ++m)
-      DD[m] = dd[m] - (Gu[0][m] * dphi[0] + Gu[1][m] * dphi[1] +
-                       Gu[2][m] * dphi[2]);
-    const T trDD = gu[0] * DD[0] + gu[3] * DD[3] + gu[5] * DD[5] +
-                   T(2) * (gu[1] * DD[1] + gu[2] * DD[2] + gu[4] * DD[4]);
-    const T dphi2 =
-        gu[0] * dphi[0] * dphi[0] + gu[3] * dphi[1] * dphi[1] +
-        gu[5] * dphi[2] * dphi[2] +
-        T(2) * (gu[1] * dphi[0] * dphi[1] + gu[2] * dphi[0] * dphi[2] +
-                gu[4] * dphi[1] * dphi[2]);
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-      for (int j = i; j < 3; ++j) {
-        const int m = S(i, j);
-        Rt[m] += T(-2) * DD[m] - T(2) * gt[m] * trDD +
-                 T(4) * dphi[i] * dphi[j] - T(4) * gt[m] * dphi2;
-      }
+    phi_ricci<T>(gt, gu, Gu, dphi, dd, Rt);
   }
 
   // ---- A (advection only) ------------------------------------------------------
@@ -493,72 +660,13 @@ __device__ __forceinline__ void point_rhs(const L& ld, const Sp& sp,
     dd[5] = d2[2];
     BSSN_PHASE();
     mixed_all<ORDER, T>(ld, ALP, ihxy, ihxz, ihyz, dd[1], dd[2], dd[4]);
-    const T em4phi = t_exp<T>(T(-4) * phi);
-    // A~^i_j, A~^ij and A~_ij A~^ij
-    T Aud[3][3];
+    T rA[6];
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
+    for (int m = 0; m < 6; ++m) rA[m] = r[AXX + m];
+    lapse_terms<T>(gt, gu, Gu, At, Rt, t_exp<T>(T(-4) * phi), dphi, trK,
+                   alpha, dalp, dd, rA, r[TRK], Tg);
 #pragma unroll
-      for (int j = 0; j < 3; ++j)
-        Aud[i][j] = gu[S(i, 0)] * At[S(0, j)] + gu[S(i, 1)] * At[S(1, j)] +
-                    gu[S(i, 2)] * At[S(2, j)];
-    T Auu[6];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-      for (int j = i; j < 3; ++j)
-        Auu[S(i, j)] = Aud[i][0] * gu[S(0, j)] + Aud[i][1] * gu[S(1, j)] +
-                       Aud[i][2] * gu[S(2, j)];
-    const T AA = At[0] * Auu[0] + At[3] * Auu[3] + At[5] * Auu[5] +
-                 T(2) * (At[1] * Auu[1] + At[2] * Auu[2] + At[4] * Auu[4]);
-    T DD[6], X[6];
-#pragma unroll
-    for (int m = 0; m < 6; ++m)
-      DD[m] = dd[m] - (Gu[0][m] * dalp[0] + Gu[1][m] * dalp[1] +
-                       Gu[2][m] * dalp[2]);
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-      for (int j = i; j < 3; ++j) {
-        const int m = S(i, j);
-        X[m] = alpha * Rt[m] - DD[m] +
-               T(2) * (dphi[i] * dalp[j] + dphi[j] * dalp[i]);
-      }
-    const T trX = gu[0] * X[0] + gu[3] * X[3] + gu[5] * X[5] +
-                  T(2) * (gu[1] * X[1] + gu[2] * X[2] + gu[4] * X[4]);
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-      for (int j = i; j < 3; ++j) {
-        const int m = S(i, j);
-        T s = em4phi * (X[m] - gt[m] * trX * T(1.0 / 3.0)) +
-              alpha * trK * At[m];
-        s -= T(2) * alpha *
-             (At[S(i, 0)] * Aud[0][j] + At[S(i, 1)] * Aud[1][j] +
-              At[S(i, 2)] * Aud[2][j]);
-        r[AXX + m] += s;
-      }
-    const T trDD = gu[0] * DD[0] + gu[3] * DD[3] + gu[5] * DD[5] +
-                   T(2) * (gu[1] * DD[1] + gu[2] * DD[2] + gu[4] * DD[4]);
-    const T dpda =
-        gu[0] * dphi[0] * dalp[0] + gu[3] * dphi[1] * dalp[1] +
-        gu[5] * dphi[2] * dalp[2] +
-        gu[1] * (dphi[0] * dalp[1] + dphi[1] * dalp[0]) +
-        gu[2] * (dphi[0] * dalp[2] + dphi[2] * dalp[0]) +
-        gu[4] * (dphi[1] * dalp[2] + dphi[2] * dalp[1]);
-    r[TRK] += -em4phi * (trDD + T(2) * dpda) +
-              alpha * (AA + trK * trK * T(1.0 / 3.0));
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const T GA = Gu[i][0] * Auu[0] + Gu[i][3] * Auu[3] + Gu[i][5] * Auu[5] +
-                   T(2) * (Gu[i][1] * Auu[1] + Gu[i][2] * Auu[2] +
-                           Gu[i][4] * Auu[4]);
-      const T Ad = Auu[S(i, 0)] * dalp[0] + Auu[S(i, 1)] * dalp[1] +
-                   Auu[S(i, 2)] * dalp[2];
-      const T Ap = Auu[S(i, 0)] * dphi[0] + Auu[S(i, 1)] * dphi[1] +
-                   Auu[S(i, 2)] * dphi[2];
-      Tg[i] += T(-2) * Ad + T(2) * alpha * (GA + T(6) * Ap);
-    }
+    for (int m = 0; m < 6; ++m) r[AXX + m] = rA[m];
   }
 
   // ---- beta^k: shift terms of gt, A~, Gt ------------------------------------
@@ -579,19 +687,12 @@ __device__ __forceinline__ void point_rhs(const L& ld, const Sp& sp,
     dd[5] = d2[2];
     BSSN_PHASE();
     mixed_all<ORDER, T>(ld, BETX + k, ihxy, ihxz, ihyz, dd[1], dd[2], dd[4]);
-    Tg[k] += gu[0] * dd[0] + gu[3] * dd[3] + gu[5] * dd[5] +
-             T(2) * (gu[1] * dd[1] + gu[2] * dd[2] + gu[4] * dd[4]);
-    Tg[k] += Gd[0] * db[0] + Gd[1] * db[1] + Gd[2] * db[2];
+    T rA[6];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) V[j] += dd[S(j, k)];
-    divb += db[k];
+    for (int m = 0; m < 6; ++m) rA[m] = r[AXX + m];
+    shift_terms<T>(k, gt, gu, At, Gd, db, dd, rg, rA, Tg, V, divb);
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-      for (int j = i; j < 3; ++j) {
-        rg[S(i, j)] += gt[S(k, i)] * db[j] + gt[S(k, j)] * db[i];
-        r[AXX + S(i, j)] += At[S(k, i)] * db[j] + At[S(k, j)] * db[i];
-      }
+    for (int m = 0; m < 6; ++m) r[AXX + m] = rA[m];
   }
 #pragma unroll
   for (int i = 0; i < 3; ++i)

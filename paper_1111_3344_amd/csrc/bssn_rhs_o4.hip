@@ -1,6 +1,6 @@
 // bssn_rhs_o4.hip -- order-4 instantiations of the stage kernels.
 #include "bssn_kernels.h"
-#include "bssn_lds.h"
+#include "bssn_split.h"
 #include "bssn_stage.h"
 
 namespace bssn {
