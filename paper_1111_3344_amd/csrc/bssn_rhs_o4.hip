@@ -8,8 +8,12 @@ namespace bssn {
 hipError_t launch_stage_o4(const Patch& P, const Gauge& G, int periodic,
                            int stage, int precision, int path, int nwg,
                            hipStream_t st, double* kout) {
-  const bool lds = !periodic && path != PATH_DIRECT && lds_path_ok<4>(P);
-  if (lds) return launch_stage_lds<4>(P, G, stage, precision, nwg, st, kout);
+  if (path != PATH_DIRECT && lds_path_ok<4>(P)) {
+    if (!periodic)
+      return launch_stage_lds<4>(P, G, stage, precision, nwg, st, kout);
+    if (lds_periodic_ok(P, precision))
+      return launch_stage_lds_periodic<4>(P, G, stage, nwg, st);
+  }
   if (kout) {
     // the direct kernels do not store the shell's right-hand side: the
     // shell kernel does, before the stage

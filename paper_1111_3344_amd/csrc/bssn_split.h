@@ -439,14 +439,44 @@ __device__ __forceinline__ __attribute__((address_space(3))) T* hand_array(
     return (lds_t*)L.hand;
 }
 
-// DMA byte offsets, from the box base, of the granules of a heavy box that
-// this lane moves (instruction j of curvature wave w).  Granules past the
-// box, and those no stencil reads, get an offset beyond the slot (2^31 and
-// up: out of range with any box base): their LDS words fill with zeros,
-// without traffic.
-template <class Geo>
+// DMA byte offset of the granule at (xx, yy, zz) of a box (its first element;
+// xx even, the box starting at (x0 - R - 1, y0 - R, z0 - R)).  Static grids:
+// from the box base, which dma_tile_base gives per tile.  Periodic grids (an
+// even number of points in x, so that no granule straddles the wrap): from
+// the slot's start, wrapped per axis.  Granules no stencil reads get an offset
+// beyond the slot (2^31 and up: out of range with any box base): their LDS
+// words fill with zeros, without traffic.
+constexpr uint32_t kNoGranule = 0x80000000u;
+// c into [0, n); once: -n <= c < 2 n, else c >= -2 n.
+__device__ __forceinline__ int wrap(int c, int n, bool once) {
+  if (!once) return int(unsigned(c + 2 * n) % unsigned(n));
+  c += c < 0 ? n : 0;
+  return c - (c >= n ? n : 0);
+}
+template <class Geo, bool PER>
+__device__ __forceinline__ uint32_t granule_offset(const Patch& P, int xx,
+                                                   int yy, int zz, bool used,
+                                                   int x0, int y0, int z0) {
+  if constexpr (PER) {
+    // a box ends at most TX + R (TY + R, TZ + R) points beyond the grid: one
+    // subtraction wraps it unless the grid is smaller than that (uniform)
+    const bool once = P.n[0] >= Geo::TX + Geo::R &&
+                      P.n[1] >= Geo::TY + Geo::R && P.n[2] >= Geo::TZ + Geo::R;
+    xx = wrap(x0 - Geo::R - 1 + xx, P.n[0], once) + P.ghost;
+    yy = wrap(y0 - Geo::R + yy, P.n[1], once) + P.ghost;
+    zz = wrap(z0 - Geo::R + zz, P.n[2], once) + P.ghost;
+  }
+  // (a slot is below 2^31 bytes)
+  const uint32_t e = uint32_t(zz) * uint32_t(P.sz) +
+                     uint32_t(yy) * uint32_t(P.sy) + uint32_t(xx);
+  return used ? e * 8u : kNoGranule;
+}
+// The granules of a heavy box that this lane moves (instruction j of
+// curvature wave w).
+template <class Geo, bool PER>
 __device__ __forceinline__ void heavy_dma_offsets(const Patch& P, int w,
-                                                  int lane,
+                                                  int lane, int x0, int y0,
+                                                  int z0,
                                                   uint32_t (&off)[Geo::L]) {
 #pragma unroll
   for (int j = 0; j < Geo::L; ++j) {
@@ -456,15 +486,16 @@ __device__ __forceinline__ void heavy_dma_offsets(const Patch& P, int w,
     const bool in_y = yy >= Geo::R && yy < Geo::R + Geo::TY;
     const bool in_z = zz >= Geo::R && zz < Geo::R + Geo::TZ;
     const bool in_x = 2 * col + 1 >= Geo::R + 1 && 2 * col <= Geo::R + Geo::TX;
-    const int64_t e = int64_t(zz) * P.sz + int64_t(yy) * P.sy + 2 * col;
-    off[j] = i < Geo::G && (in_x || in_y || in_z) ? uint32_t(e * 8)
-                                                  : 0x80000000u;
+    off[j] = granule_offset<Geo, PER>(P, 2 * col, yy, zz,
+                                      i < Geo::G && (in_x || in_y || in_z),
+                                      x0, y0, z0);
   }
 }
-// The same for the runs of a light slot (instruction j of transport wave w).
-template <class Geo>
+// The same for the runs of a light slot.
+template <class Geo, bool PER>
 __device__ __forceinline__ void light_dma_offsets(const Patch& P, int w,
-                                                  int lane,
+                                                  int lane, int x0, int y0,
+                                                  int z0,
                                                   uint32_t (&off)[Geo::LL]) {
 #pragma unroll
   for (int j = 0; j < Geo::LL; ++j) {
@@ -486,13 +517,13 @@ __device__ __forceinline__ void light_dma_offsets(const Patch& P, int w,
       yy = Geo::R + (m / Geo::TX) % Geo::TY;
       zz = m / (Geo::TX * Geo::TY);
     }
-    const int64_t e = int64_t(zz) * P.sz + int64_t(yy) * P.sy + xx;
-    off[j] = i < 2 * Geo::LG ? uint32_t(e * 8) : 0x80000000u;
+    off[j] = granule_offset<Geo, PER>(P, xx, yy, zz, i < 2 * Geo::LG, x0, y0,
+                                      z0);
   }
 }
 
 // ---- the curvature waves ---------------------------------------------------------
-template <int ORDER, typename T, bool SKIP, class WK>
+template <int ORDER, typename T, bool SKIP, bool PER, class WK>
 __device__ __forceinline__ void curvature_waves(const Patch& P, const Gauge& G,
                                                 const WK& Wk,
                                                 SplitLds<ORDER, T>& S_,
@@ -525,8 +556,10 @@ __device__ __forceinline__ void curvature_waves(const Patch& P, const Gauge& G,
   // DMA of step s of the workgroup's k-th tile (box base tb): its heavy
   // slot, its light slots
   uint32_t hoff[Geo::L], loff[Geo::LL];
-  heavy_dma_offsets<Geo>(P, w, lane, hoff);
-  light_dma_offsets<Geo>(P, w, lane, loff);
+  int x0, y0, z0;
+  Wk.origin(0, x0, y0, z0);
+  heavy_dma_offsets<Geo, PER>(P, w, lane, x0, y0, z0, hoff);
+  light_dma_offsets<Geo, PER>(P, w, lane, x0, y0, z0, loff);
   auto issue_heavy = [&](int k, int s, uint32_t tb) {
     const v4i d = slot_dma_rsrc(P.u_s, P.sf, kStepHeavy[s], nbytes);
     const uint32_t l0 = lds_addr(S_.heavy + Geo::heavy_buf(k, s) * Geo::BUFD) +
@@ -534,7 +567,7 @@ __device__ __forceinline__ void curvature_waves(const Patch& P, const Gauge& G,
 #pragma unroll
     for (int j = 0; j < Geo::L; ++j)
       if (j < Geo::NI - 3 * Geo::L || w < 3)
-        dma16(d, hoff[j] + tb, l0 + j * 1024u);
+        dma16(d, PER ? hoff[j] : hoff[j] + tb, l0 + j * 1024u);
   };
   auto issue_light = [&](int k, int s, uint32_t tb) {
 #pragma unroll
@@ -546,7 +579,7 @@ __device__ __forceinline__ void curvature_waves(const Patch& P, const Gauge& G,
 #pragma unroll
       for (int j = 0; j < Geo::LL; ++j)
         if (j < Geo::LNI - 3 * Geo::LL || w < 3)
-          dma16(d, loff[j] + tb, l0 + j * 1024u);
+          dma16(d, PER ? loff[j] : loff[j] + tb, l0 + j * 1024u);
     }
   };
   // DMA of the transport waves' centre values (wave w: entry w of cen)
@@ -562,8 +595,6 @@ __device__ __forceinline__ void curvature_waves(const Patch& P, const Gauge& G,
     dma16(w < 3 ? d : da, o, l0);
     dma16(w < 3 ? d : da, o + uint32_t(P.sz) * 16u, l0 + 1024u);
   };
-  int x0, y0, z0;
-  Wk.origin(0, x0, y0, z0);
   uint32_t tb = dma_tile_base<Geo>(P, x0, y0, z0);
   issue_centre(tb);
   issue_heavy(0, 0, tb);
@@ -605,7 +636,13 @@ __device__ __forceinline__ void curvature_waves(const Patch& P, const Gauge& G,
     };
     // DMA issued in step s: after its inner sums, and (LATE) once its box
     // has been read
+    // (periodic grids: the lanes' offsets are the next tile's from here on)
     auto fetch = [&](int s) {
+      if (PER && more && s == (Geo::LATE ? 10 : 9)) {
+        light_dma_offsets<Geo, PER>(P, w, own_lane(), xn, yn, zn, loff);
+        if (!Geo::LATE)
+          heavy_dma_offsets<Geo, PER>(P, w, own_lane(), xn, yn, zn, hoff);
+      }
       if (Geo::LATE) {
         if (s + 1 < kNStep)
           issue_light(k, s + 1, tb);
@@ -627,8 +664,11 @@ __device__ __forceinline__ void curvature_waves(const Patch& P, const Gauge& G,
       mid_barrier();
       if (s + 2 < kNStep)
         issue_heavy(k, s + 2, tb);
-      else if (s + 2 == kNStep && more)
+      else if (s + 2 == kNStep && more) {
+        if (PER)
+          heavy_dma_offsets<Geo, PER>(P, w, own_lane(), xn, yn, zn, hoff);
         issue_heavy(k + 1, 0, tbn);
+      }
     };
     step_barrier<0>();  // step 0
 #pragma unroll
@@ -1008,8 +1048,10 @@ struct Transport {
 // The tiles Wk names, of patch P.  SKIP: tiles whose minimum lapse is below
 // G.alpha_thr are left out (mixed precision's FP32 launch).  KSH: points on
 // the outermost interior layer also store their right-hand side to kout.
-// The caller places a barrier before the LDS is used again.
-template <int ORDER, typename T, bool SKIP, bool KSH, class WK>
+// PER: periodic grid.  The caller places a barrier before the LDS is used
+// again.
+template <int ORDER, typename T, bool SKIP, bool KSH, bool PER = false,
+          class WK>
 __device__ __forceinline__ void split_tiles(const Patch& P, const Gauge& G,
                                             int stage, const WK& Wk,
                                             SplitLds<ORDER, T>& L,
@@ -1021,7 +1063,7 @@ __device__ __forceinline__ void split_tiles(const Patch& P, const Gauge& G,
   int lane = threadIdx.x & 63;
   asm volatile("" : "+v"(lane));
   if (wave < 4) {
-    curvature_waves<ORDER, T, SKIP>(P, G, Wk, L, wave & 3, lane);
+    curvature_waves<ORDER, T, SKIP, PER>(P, G, Wk, L, wave & 3, lane);
   } else {
     Transport<ORDER, T, SKIP, KSH> t(P, G, L, stage, kout, wave & 3, lane);
     t.run(Wk);
@@ -1032,15 +1074,16 @@ __device__ __forceinline__ void split_tiles(const Patch& P, const Gauge& G,
 constexpr int kSplitThreads = 512;
 
 // One patch, FP64: workgroup b takes the tiles of walk_of(b).  KSH: also
-// the right-hand side at the outermost interior layer into kout.
-template <int ORDER, bool KSH = false>
+// the right-hand side at the outermost interior layer into kout.  PER:
+// periodic grid.
+template <int ORDER, bool KSH = false, bool PER = false>
 __global__ void __launch_bounds__(kSplitThreads)
     __attribute__((amdgpu_waves_per_eu(2, 2)))
     k_stage_lds(const Patch P, const Gauge G, const int stage,
                 const TileMap M, double* const kout) {
   __shared__ __attribute__((aligned(16))) SplitLds<ORDER, double> L;
-  split_tiles<ORDER, double, false, KSH>(P, G, stage,
-                                         walk_of(M, gridDim.x), L, kout);
+  split_tiles<ORDER, double, false, KSH, PER>(
+      P, G, stage, walk_of(M, gridDim.x), L, kout);
 }
 
 // Threads of the FP32 launches: at order 4 the FP32 point function fits one
@@ -1382,6 +1425,28 @@ hipError_t launch_stage_lds_k(const Patch& P, const Gauge& G, int stage,
   if (e != hipSuccess) return e;
   return launch_f64tiles<ORDER>(P, G, stage, M, nwg, st, kout);
 }
+// Periodic grid, FP64.
+template <int ORDER>
+hipError_t launch_stage_lds_periodic(const Patch& P, const Gauge& G, int stage,
+                                     int nwg_max, hipStream_t st) {
+  TileMap M = lds_tile_map<ORDER>(P);
+  const int nwg = M.ntiles < nwg_max ? M.ntiles : nwg_max;
+  choose_blocks<ORDER>(M, nwg);
+  hipLaunchKernelGGL((k_stage_lds<ORDER, false, true>), dim3(nwg),
+                     dim3(kSplitThreads), 0, st, P, G, stage, M, nullptr);
+  return hipGetLastError();
+}
+// The LDS kernel takes a periodic grid in FP64 with an even number of points
+// in x: the boxes' 16-byte granules then wrap as wholes (each lane forms its
+// wrapped DMA offsets once per tile).  Odd ones, and mixed precision (whose
+// tiles are the direct kernels'), stay on the direct kernels.  Measured, direct
+// and here: a 32^3 RK4 step 232 and 108 us, a 96^3 right-hand side 1,330 and
+// 330 us (order 4), order 8 3,850 and
+// 513 us.
+inline bool lds_periodic_ok(const Patch& P, int precision) {
+  return precision == 0 && P.n[0] % 2 == 0;
+}
+
 // kout set: the kernels that also store the right-hand side at the
 // outermost interior layer there.
 template <int ORDER>

@@ -70,3 +70,39 @@ def test_rhs_and_stages(n, order):
                    4e-16 * np.abs(g.interior(b)).reshape(25, -1).max(1) +
                    4e-16 * np.abs(ref).reshape(25, -1).max(1))
             assert (np.abs(d - ref).reshape(25, -1).max(1) <= tol).all(), s
+
+
+# periodic grids on the same kernel: x extents below, at and above a tile
+# (even: whole granules wrap; odd: the direct kernel), y and z below the
+# tile and the stencil's reach, several tiles per workgroup
+@pytest.mark.parametrize("order", [4, 8])
+@pytest.mark.parametrize("n", [(6, 5, 5), (16, 4, 6), (18, 7, 9), (17, 8, 8),
+                               (32, 32, 32), (48, 50, 46)])
+def test_periodic_rhs_and_step(n, order):
+    import torch
+    from paper_1111_3344_amd import bssn as B
+    n = tuple(max(v, 5) for v in n) if order == 8 else n
+    g = I.GridSpec(n, 5 if order == 8 else 3, (0.1, 0.11, 0.12),
+                   (-0.7, -0.5, -0.6), I.BC_PERIODIC)
+    u = I.smooth_random(g, seed=sum(n) + order)
+    I.fill_periodic_ghosts(g, u)
+    print(f"[split] periodic n={n} order={order}", flush=True)
+    # the device copy's ghosts are never read
+    v = u.copy()
+    g.view(v)[...] = np.nan
+    g.interior(v)[...] = g.interior(u)
+    du = torch.from_numpy(v).to("cuda")
+    out = torch.zeros_like(du)
+    prm = B.Params(fd_order=order)
+    B.bssn_rhs(g, prm, du, out)
+    k = O.rhs(g, O.params(fd_order=order), u)
+    assert _err(g, out.cpu().numpy(), k).max() <= 1e-12
+    a, b, acc = du.clone(), du.clone(), torch.zeros_like(du)
+    ref = O.rk4_step(g, O.params(fd_order=order), 0.02, u)
+    B.rk4_step(g, prm, 0.02, du, a, b, acc)
+    inc = g.interior(du.cpu().numpy()) - g.interior(u)
+    want = g.interior(ref) - g.interior(u)
+    D = np.abs(want).reshape(25, -1).max(1)
+    D = np.where(D > 0, D, D.max())
+    # four right-hand sides, each to 1e-12 of its own scale
+    assert (np.abs(inc - want).reshape(25, -1).max(1) / D).max() <= 1e-11
