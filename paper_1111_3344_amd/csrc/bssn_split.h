@@ -1336,9 +1336,11 @@ inline TileMap lds_tile_map(const Patch& P) {
 
 // Blocked walk (Walk with bx > 0) for a launch of 256 or 512 workgroups
 // (one or two per CU): the first block shape of nwg / 8 tiles that divides
-// the tile grid and leaves every XCD at least one block; otherwise the
-// contiguous walk.  Order 8 (a 14-plane box) measured best with blocks 2
-// tiles deep in z, order 4 with 4.
+// the tile grid and gives no workgroup more than 5% more tiles than the even
+// split of the contiguous walk does (the blocks' cache sharing is worth 3-10%;
+// 18 block columns on 8 XCDs, a 96^3 grid, would cost 29%: 330 against
+// 290 us per order-4 right-hand side); otherwise the contiguous walk.  Order 8
+// (a 14-plane box) measured best with blocks 2 tiles deep in z, order 4 with 4.
 template <int ORDER>
 inline void choose_blocks(TileMap& M, int nwg) {
   static const int s32[][3] = {
@@ -1349,9 +1351,12 @@ inline void choose_blocks(TileMap& M, int nwg) {
                                {2, 8, 4}, {4, 2, 8}, {8, 8, 1}};
   M.bx = M.by = M.bz = 0;
   if (nwg != 256 && nwg != 512) return;
+  const int64_t even = (M.ntiles + nwg - 1) / nwg;
   for (const auto& b : (nwg == 256 ? s32 : s64)) {
     if (M.ntx % b[0] || M.nty % b[1] || M.ntz % b[2]) continue;
-    if ((M.ntx / b[0]) * (M.nty / b[1]) < 8) continue;
+    const int64_t cols = int64_t(M.ntx / b[0]) * (M.nty / b[1]);
+    const int64_t most = (cols + 7) / 8 * (M.ntz / b[2]);
+    if (most * 20 > even * 21) continue;
     M.bx = b[0];
     M.by = b[1];
     M.bz = b[2];
@@ -1441,7 +1446,7 @@ hipError_t launch_stage_lds_periodic(const Patch& P, const Gauge& G, int stage,
 // wrapped DMA offsets once per tile).  Odd ones, and mixed precision (whose
 // tiles are the direct kernels'), stay on the direct kernels.  Measured, direct
 // and here: a 32^3 RK4 step 232 and 108 us, a 96^3 right-hand side 1,330 and
-// 330 us (order 4), order 8 3,850 and
+// 330 us (order 4; 290 with the walk rule of choose_blocks), order 8 3,850 and
 // 513 us.
 inline bool lds_periodic_ok(const Patch& P, int precision) {
   return precision == 0 && P.n[0] % 2 == 0;
