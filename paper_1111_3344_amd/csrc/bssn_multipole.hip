@@ -3,12 +3,11 @@
 // multipole module projects a field interpolated onto spheres onto
 // spin-weighted spherical harmonics, C^lm = integral conj(sY_lm) u r^2 dOmega).
 //
-// Four launches:
-//   k_gl_nodes      Gauss-Legendre nodes and weights in cos(theta), by Newton
-//                   iteration on the Legendre recurrence (one thread per node);
-//   k_sphere_interp one thread per sphere point (theta_j, phi_k): the
-//                   tricubic interpolation of the real and imaginary parts
-//                   (4 x 4 x 4 storage points, block clamped into the grid);
+// Three launches:
+//   k_sphere_interp four threads per sphere point (theta_j, phi_k): the
+//                   Gauss-Legendre node theta_j, and the tricubic
+//                   interpolation of the real and imaginary parts (4 x 4 x 4
+//                   storage points, block clamped into the grid);
 //   k_multipole     one workgroup per (l, m, chunk of the points): the sum
 //                   of conj(sY_lm) u w_j (2 pi / n_phi) over its points, a
 //                   fixed-order tree reduction;
@@ -17,7 +16,14 @@
 // sY_lm (Goldberg's sum) is evaluated with half-angle powers,
 //   sin^{2l-k}(theta/2) cos^{k}(theta/2), k = 2r + s - m in [0, 2l],
 // so no cotangent is formed.
+// A sphere is a few thousand points, so every launch is bound by the latency
+// of its serial chains, not by memory.  64 x 128 points with l <= 8: 33 us for
+// the three, against 74 us when the nodes were a launch of their own with a
+// division per recurrence step (22), the interpolation took one thread per
+// point (25) and every point formed its binomials (21).
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "bssn_internal.h"
 #include "bssn_kernels.h"
@@ -48,46 +54,63 @@ __device__ __forceinline__ double binom(int n, int k) {
   return r;
 }
 
-// Nodes ascending in x = cos(theta).
-__global__ void __launch_bounds__(64)
-    k_gl_nodes(const int n, double* __restrict__ x, double* __restrict__ w) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
+// P_n(z) in p1 and P_{n-1}(z) in p0, rec[k] = {(2k - 1)/k, (k - 1)/k}: with the
+// divisions in the table the chain of a step is one FMA.
+__device__ __forceinline__ void legendre(const double2* rec, int n, double z,
+                                         double& p0, double& p1) {
+  p0 = 1.0;
+  p1 = z;
+#pragma unroll 4
+  for (int k = 2; k <= n; ++k) {
+    const double2 c = rec[k];
+    const double p2 = c.x * z * p1 - c.y * p0;
+    p0 = p1;
+    p1 = p2;
+  }
+}
+
+// Gauss-Legendre node j of n (ascending in x = cos(theta)) and its weight, by
+// Newton iteration on the Legendre recurrence.
+__device__ __forceinline__ void gl_node(const double2* rec, int n, int j,
+                                        double& x, double& w) {
   const int jd = n - 1 - j;  // the guess below is descending in j
   double z = cos(M_PI * (jd + 0.75) / (n + 0.5));
-  double dp = 1.0;
+  double p0, p1;
   for (int it = 0; it < 100; ++it) {
-    double p0 = 1.0, p1 = z;
-    for (int k = 2; k <= n; ++k) {
-      const double p2 = ((2.0 * k - 1.0) * z * p1 - (k - 1.0) * p0) / k;
-      p0 = p1;
-      p1 = p2;
-    }
-    if (n == 1) p0 = 1.0;
-    dp = n * (z * p1 - p0) / (z * z - 1.0);
+    legendre(rec, n, z, p0, p1);
+    const double dp = n * (z * p1 - p0) / (z * z - 1.0);
     const double dz = p1 / dp;
     z -= dz;
     if (fabs(dz) <= 1e-15 * fabs(z)) break;  // dz = 0 at the middle node
   }
   // the weight from the derivative at the converged node
-  double p0 = 1.0, p1 = z;
-  for (int k = 2; k <= n; ++k) {
-    const double p2 = ((2.0 * k - 1.0) * z * p1 - (k - 1.0) * p0) / k;
-    p0 = p1;
-    p1 = p2;
-  }
-  dp = n * (z * p1 - p0) / (z * z - 1.0);
-  x[j] = z;
-  w[j] = 2.0 / ((1.0 - z * z) * dp * dp);
+  legendre(rec, n, z, p0, p1);
+  const double dp = n * (z * p1 - p0) / (z * z - 1.0);
+  x = z;
+  w = 2.0 / ((1.0 - z * z) * dp * dp);
 }
 
-__global__ void __launch_bounds__(64)
-    k_sphere_interp(const MultipoleArgs A, const double* __restrict__ x,
-                    double* __restrict__ val) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+// Lane q of a point's four takes the z plane q of its 4 x 4 x 4 block, so its
+// 32 loads are in flight together.  Each point works out its own node (one
+// Newton iteration per wave either way); the first of a row leaves it for the
+// next launch.
+__global__ void __launch_bounds__(256)
+    k_sphere_interp(const MultipoleArgs A, double* __restrict__ xs,
+                    double* __restrict__ ws, double* __restrict__ val) {
+  extern __shared__ double2 rec[];
+  for (int k = 2 + threadIdx.x; k <= A.ntheta; k += 256)
+    rec[k] = {(2.0 * k - 1.0) / k, (k - 1.0) / k};
+  __syncthreads();
+  const int p = (blockIdx.x * 256 + threadIdx.x) >> 2, kk = threadIdx.x & 3;
   if (p >= A.ntheta * A.nphi) return;
   const int j = p / A.nphi, k = p % A.nphi;
-  const double ct = x[j], st = sqrt(fmax(0.0, 1.0 - ct * ct));
+  double ct, wj;
+  gl_node(rec, A.ntheta, j, ct, wj);
+  if (k == 0 && kk == 0) {
+    xs[j] = ct;
+    ws[j] = wj;
+  }
+  const double st = sqrt(fmax(0.0, 1.0 - ct * ct));
   const double ph = 2.0 * M_PI * k / A.nphi;
   const double pos[3] = {A.centre[0] + A.radius * st * cos(ph),
                          A.centre[1] + A.radius * st * sin(ph),
@@ -116,54 +139,76 @@ __global__ void __launch_bounds__(64)
     }
   }
   double re = 0.0, im = 0.0;
-  const int64_t base = int64_t(b[2]) * A.sz + int64_t(b[1]) * A.sy + b[0];
-  for (int kk = 0; kk < 4; ++kk)
+  const int64_t base =
+      int64_t(b[2] + kk) * A.sz + int64_t(b[1]) * A.sy + b[0];
+  const double wz = kk == 0   ? wt[2][0]
+                    : kk == 1 ? wt[2][1]
+                    : kk == 2 ? wt[2][2]
+                              : wt[2][3];
 #pragma unroll
-    for (int jj = 0; jj < 4; ++jj)
+  for (int jj = 0; jj < 4; ++jj)
 #pragma unroll
-      for (int ii = 0; ii < 4; ++ii) {
-        const double w = wt[2][kk] * wt[1][jj] * wt[0][ii];
-        const int64_t o = base + kk * A.sz + jj * A.sy + ii;
-        re += w * A.re[o];
-        if (A.im) im += w * A.im[o];
-      }
-  val[2 * p] = re;
-  val[2 * p + 1] = im;
+    for (int ii = 0; ii < 4; ++ii) {
+      const double w = wz * wt[1][jj] * wt[0][ii];
+      const int64_t o = base + jj * A.sy + ii;
+      re += w * A.re[o];
+      if (A.im) im += w * A.im[o];
+    }
+#pragma unroll
+  for (int h = 1; h < 4; h *= 2) {
+    re += __shfl_xor(re, h, 64);
+    im += __shfl_xor(im, h, 64);
+  }
+  if (kk == 0) {
+    val[2 * p] = re;
+    val[2 * p + 1] = im;
+  }
 }
 
+// With r from r0 to r1 the powers in Goldberg's sum step by cos^2 up and sin^2
+// down, so a point's sum is a homogeneous Horner scheme over coefficients that
+// the workgroup forms once (l <= 16 and |s| <= 8 by the entry point's checks, so
+// there are at most 25).
 __global__ void __launch_bounds__(256)
     k_multipole(const MultipoleArgs A, const double* __restrict__ x,
                 const double* __restrict__ w, const double* __restrict__ val,
                 const int nchunk, double* __restrict__ part) {
-  __shared__ double sre[256], sim[256];
+  __shared__ double coef[32], red[2][4];
   const int q = blockIdx.x / nchunk, chunk = blockIdx.x % nchunk;
+  const int t = threadIdx.x;
   int l = 0;
   while ((l + 1) * (l + 1) <= q) ++l;
   const int m = q - l * l - l;
   const int s = A.spin;
   double are = 0.0, aim = 0.0;
   if (l >= (s < 0 ? -s : s)) {
-    const double pre =
-        ((m & 1) ? -1.0 : 1.0) *
-        sqrt(fact(l + m) * fact(l - m) * (2 * l + 1) /
-             (4.0 * M_PI * fact(l + s) * fact(l - s)));
+    const int r0 = m - s > 0 ? m - s : 0;
+    const int r1 = l - s < l + m ? l - s : l + m;
+    if (t <= r1 - r0) {
+      const int r = r0 + t;
+      const double pre =
+          ((m & 1) ? -1.0 : 1.0) *
+          sqrt(fact(l + m) * fact(l - m) * (2 * l + 1) /
+               (4.0 * M_PI * fact(l + s) * fact(l - s)));
+      const double sign = ((l - r - s) & 1) ? -1.0 : 1.0;
+      coef[t] = pre * sign * binom(l - s, r) * binom(l + s, r + s - m);
+    }
+    __syncthreads();
     const double dphi = 2.0 * M_PI / A.nphi;
     const int npts = A.ntheta * A.nphi;
-    for (int p = chunk * 256 + threadIdx.x; p < npts; p += nchunk * 256) {
+    const int elo = 2 * r0 + s - m, ehi = 2 * l - (2 * r1 + s - m);
+    for (int p = chunk * 256 + t; p < npts; p += nchunk * 256) {
       const int j = p / A.nphi, k = p % A.nphi;
       const double ct = x[j];
-      const double sh = sqrt(fmax(0.0, 0.5 * (1.0 - ct)));
-      const double ch = sqrt(fmax(0.0, 0.5 * (1.0 + ct)));
-      double sum = 0.0;
-      for (int r = 0; r <= l - s; ++r) {
-        const int kb = r + s - m;
-        if (kb < 0 || kb > l + s) continue;
-        const int e = 2 * r + s - m;  // cot power, in [0, 2l]
-        const double sign = ((l - r - s) & 1) ? -1.0 : 1.0;
-        sum += sign * binom(l - s, r) * binom(l + s, kb) *
-               ipow(sh, 2 * l - e) * ipow(ch, e);
+      const double s2 = fmax(0.0, 0.5 * (1.0 - ct));
+      const double c2 = fmax(0.0, 0.5 * (1.0 + ct));
+      double y = coef[0], cp = 1.0;
+      for (int i = 1; i <= r1 - r0; ++i) {
+        cp *= c2;
+        y = y * s2 + coef[i] * cp;
       }
-      const double y = pre * sum;  // real part of sY_lm without e^{i m phi}
+      // real part of sY_lm without e^{i m phi}
+      y *= ipow(sqrt(s2), ehi) * ipow(sqrt(c2), elo);
       double sn, cs;
       sincos(m * (dphi * k), &sn, &cs);
       // conj(Y) u = y (cos - i sin)(u_re + i u_im)
@@ -173,20 +218,19 @@ __global__ void __launch_bounds__(256)
       aim += wq * y * (cs * ui - sn * ur);
     }
   }
-  sre[threadIdx.x] = are;
-  sim[threadIdx.x] = aim;
+#pragma unroll
+  for (int h = 32; h > 0; h >>= 1) {
+    are += __shfl_xor(are, h, 64);
+    aim += __shfl_xor(aim, h, 64);
+  }
+  if ((t & 63) == 0) {
+    red[0][t >> 6] = are;
+    red[1][t >> 6] = aim;
+  }
   __syncthreads();
-  for (int h = 128; h > 0; h >>= 1) {
-    if (threadIdx.x < h) {
-      sre[threadIdx.x] += sre[threadIdx.x + h];
-      sim[threadIdx.x] += sim[threadIdx.x + h];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    part[2 * (q * nchunk + chunk)] = sre[0];
-    part[2 * (q * nchunk + chunk) + 1] = sim[0];
-  }
+  if (t < 2)
+    part[2 * (q * nchunk + chunk) + t] =
+        (red[t][0] + red[t][1]) + (red[t][2] + red[t][3]);
 }
 
 // One thread per (l, m): the chunks' partial sums added in chunk order.
@@ -197,6 +241,7 @@ __global__ void __launch_bounds__(64)
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= nq) return;
   double re = 0.0, im = 0.0;
+#pragma unroll 8
   for (int c = 0; c < nchunk; ++c) {
     re += part[2 * (q * nchunk + c)];
     im += part[2 * (q * nchunk + c) + 1];
@@ -212,17 +257,16 @@ hipError_t launch_multipole(const MultipoleArgs& A, double* work,
   double* x = work;
   double* w = work + A.ntheta;
   double* val = work + 2 * A.ntheta;
-  hipLaunchKernelGGL(k_gl_nodes, dim3((A.ntheta + 63) / 64), dim3(64), 0, st,
-                     A.ntheta, x, w);
+  const int npts = A.ntheta * A.nphi;
+  hipLaunchKernelGGL(k_sphere_interp, dim3((npts + 63) / 64), dim3(256),
+                     sizeof(double2) * (A.ntheta + 1), st, A, x, w, val);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int npts = A.ntheta * A.nphi;
-  hipLaunchKernelGGL(k_sphere_interp, dim3((npts + 63) / 64), dim3(64), 0, st,
-                     A, x, val);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
   const int nq = (A.lmax + 1) * (A.lmax + 1);
-  const int nchunk = multipole_chunks(A.ntheta, A.nphi);
+  // four points per thread repay forming the coefficients; never more chunks
+  // than the workspace has room for
+  const int nchunk =
+      std::min((npts + 1023) / 1024, multipole_chunks(A.ntheta, A.nphi));
   double* part = val + 2 * int64_t(npts);
   hipLaunchKernelGGL(k_multipole, dim3(nq * nchunk), dim3(256), 0, st, A, x,
                      w, val, nchunk, part);
