@@ -40,8 +40,8 @@
 // sums need anyway.  Measured against one wave per SIMD with the whole point
 // in each thread (RK4 step, one MI355X): 128^3 order 4 2.91 -> 2.45 ms, 256^3
 // order 4 25.4 -> 19.7 ms, 256^3 order 8 36.4 -> 28.6 ms, 83 x 61 x 45 order 4
-// 531 -> 452 us, 48 uneven patches 18.7 -> 17.1 ms; FP32 at order 8 (mixed
-// precision, 97 x 53 x 75) 1,463 -> 1,139 us.  Prefetching one step ahead
+// 531 -> 376 us, 48 uneven patches 18.7 -> 17.1 ms; FP32 at order 8 (mixed
+// precision, 97 x 53 x 75) 1,463 -> 1,112 us.  Prefetching one step ahead
 // instead of two (order 4) cost 8%, updating at the start of a step instead of
 // its end 10%; a branch around the update's loads or stores costs 10-80%, as
 // the compiler then waits for the loads at the branch.
@@ -859,9 +859,14 @@ struct Transport {
     corner = (w * Geo::H + ty) * Geo::W + tx + 1;
     const double dt = P.dt;
     pu = stage == ST_3 ? P.acc : P.u_n;
-    nu = stage == ST_RHS ? 0 : nbytes;
-    na = stage == ST_1 || stage == ST_2 ? nbytes : 0;
-    nacc = stage == ST_3 || stage == ST_RHS ? 0 : nbytes;
+    // (uniform, but only readfirstlane makes the compiler hold them in scalar
+    // registers: from vector ones every access became a loop over the lanes'
+    // descriptors, one after the other: 452 against 376 us for an RK4 step of
+    // 83 x 61 x 45, whose workgroups flush after five tiles)
+    auto uni = [](int32_t v) { return __builtin_amdgcn_readfirstlane(v); };
+    nu = uni(stage == ST_RHS ? 0 : nbytes);
+    na = uni(stage == ST_1 || stage == ST_2 ? nbytes : 0);
+    nacc = uni(stage == ST_3 || stage == ST_RHS ? 0 : nbytes);
     a_is_u = stage == ST_0;
     c1 = stage == ST_0 ? dt / 6.0 : dt / 3.0;
     c2 = stage == ST_RHS ? 1.0
@@ -884,8 +889,9 @@ struct Transport {
     constexpr int s = step_slot(ST, I);
     // (issued also where the stage needs none, with a range of 0 bytes: a
     // branch around them would wait for the loaded value at its end)
-    u[I] = bload_nt(slot_rsrc(pu, P.sf, s, nu), vc);
-    a[I] = bload_nt(slot_rsrc(P.acc, P.sf, s, na), vc);
+    const uint64_t o = slot_bytes(P.sf, s);
+    u[I] = bload_nt(rsrc_at(pu, o, nu), vc);
+    a[I] = bload_nt(rsrc_at(P.acc, o, na), vc);
     if constexpr (I < n_light(ST)) update_load<ST, I + 1>(vc, u, a);
   }
   template <int ST, int I = 0>
@@ -893,10 +899,11 @@ struct Transport {
                                                const double (&a)[3]) const {
     constexpr int s = step_slot(ST, I);
     const double k = double(r[s]);
-    bstore_nt(slot_rsrc(P.acc, P.sf, s, nacc), vcp,
+    const uint64_t o = slot_bytes(P.sf, s);
+    bstore_nt(rsrc_at(P.acc, o, nacc), vcp,
               (a_is_u ? u[I] : a[I]) + c1 * k);
-    bstore_nt(slot_rsrc(P.out, P.sf, s, nbytes), vcp, u[I] + c2 * k);
-    if constexpr (KSH) bstore_nt(slot_rsrc(kout, P.sf, s, nbytes), vsp, k);
+    bstore_nt(rsrc_at(P.out, o, nbytes), vcp, u[I] + c2 * k);
+    if constexpr (KSH) bstore_nt(rsrc_at(kout, o, nbytes), vsp, k);
     if constexpr (I < n_light(ST)) update_store<ST, I + 1>(u, a);
   }
 
@@ -1045,6 +1052,16 @@ struct Transport {
   }
 };
 
+// This thread's wave and lane.  A kernel that calls split_tiles in a loop asks
+// for the wave once and never for threadIdx again, which would hold a vector
+// register through the calls.
+__device__ __forceinline__ int wave_id() {
+  return __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+}
+__device__ __forceinline__ int lane_id() {
+  return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+}
+
 // The tiles Wk names, of patch P.  SKIP: tiles whose minimum lapse is below
 // G.alpha_thr are left out (mixed precision's FP32 launch).  KSH: points on
 // the outermost interior layer also store their right-hand side to kout.
@@ -1055,12 +1072,11 @@ template <int ORDER, typename T, bool SKIP, bool KSH, bool PER = false,
 __device__ __forceinline__ void split_tiles(const Patch& P, const Gauge& G,
                                             int stage, const WK& Wk,
                                             SplitLds<ORDER, T>& L,
-                                            double* kout) {
+                                            double* kout, int wave) {
   if (Wk.count() <= 0) return;
-  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   // (opaque: a caller's loop over several calls must not keep what both
   // kinds of waves derive from it in registers between them)
-  int lane = threadIdx.x & 63;
+  int lane = lane_id();
   asm volatile("" : "+v"(lane));
   if (wave < 4) {
     curvature_waves<ORDER, T, SKIP, PER>(P, G, Wk, L, wave & 3, lane);
@@ -1083,7 +1099,7 @@ __global__ void __launch_bounds__(kSplitThreads)
                 const TileMap M, double* const kout) {
   __shared__ __attribute__((aligned(16))) SplitLds<ORDER, double> L;
   split_tiles<ORDER, double, false, KSH, PER>(
-      P, G, stage, walk_of(M, gridDim.x), L, kout);
+      P, G, stage, walk_of(M, gridDim.x), L, kout, wave_id());
 }
 
 // Threads of the FP32 launches: at order 4 the FP32 point function fits one
@@ -1106,7 +1122,7 @@ __device__ __forceinline__ void f32_tiles(const Patch& P, const Gauge& G,
                                           int stage, const Walk& w,
                                           F32Lds<ORDER>& L, double* kout) {
   if constexpr (ORDER == 8)
-    split_tiles<8, float, true, KSH>(P, G, stage, w, L, kout);
+    split_tiles<8, float, true, KSH>(P, G, stage, w, L, kout, wave_id());
   else
     lds_tiles<KSH>(P, G, stage, w, L.ring, L.sc, kout);
 }
@@ -1202,9 +1218,9 @@ __device__ __forceinline__ double tile_lapse_min_global(const Patch& P,
 // Writes val of every thread whose flag is set to list, in thread order,
 // and returns their number (the same in every thread).  wcnt: 8 ints of
 // LDS.  Contains the barriers that make list readable afterwards.
-__device__ __forceinline__ int compact_flags(bool f, int val, int* list,
-                                             int* wcnt) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+__device__ __forceinline__ int compact_flags(bool f, int val, int wave,
+                                             int* list, int* wcnt) {
+  const int lane = lane_id();
   const uint64_t mask = __builtin_amdgcn_ballot_w64(f);
   if (lane == 0) wcnt[wave] = __builtin_popcountll(mask);
   __syncthreads();
@@ -1239,10 +1255,11 @@ __global__ void __launch_bounds__(kSplitThreads)
   // the per-wave counts of compact_flags live in the mixed-derivative
   // scratch, which is idle between split_tiles calls (the LDS is full)
   int* wcnt = (int*)L.mix;
-  const int tid = threadIdx.x;
+  const int wave = wave_id();
   int lo, hi;
   walk_range(blockIdx.x, gridDim.x, M.ntiles, lo, hi);
   for (int c0 = lo; c0 < hi; c0 += kSplitThreads) {
+    const int tid = wave * 64 + lane_id();
     bool f = false;
     int t = 0;
     if (c0 + tid < hi) {
@@ -1251,10 +1268,10 @@ __global__ void __launch_bounds__(kSplitThreads)
       tile_origin(t, M.ntx, M.ntz, x0, y0, z0);
       f = tile_lapse_min_global(P, x0, y0, z0) < G.alpha_thr;
     }
-    const int n = compact_flags(f, t, list, wcnt);
+    const int n = compact_flags(f, t, wave, list, wcnt);
     if (n > 0) {
       const ListWalk w{(const lds_int*)list, n, M.ntx, M.ntz};
-      split_tiles<ORDER, double, false, KSH>(P, G, stage, w, L, kout);
+      split_tiles<ORDER, double, false, KSH>(P, G, stage, w, L, kout, wave);
     }
     __syncthreads();  // the LDS, list and wcnt are reused
   }
@@ -1270,13 +1287,14 @@ __global__ void __launch_bounds__(kSplitThreads)
                       const int32_t* __restrict__ wstart, const Gauge G,
                       const int stage) {
   __shared__ __attribute__((aligned(16))) SplitLds<ORDER, double> L;
+  const int wave = wave_id();
   const int q = walk_pos(blockIdx.x, gridDim.x);
   const int i0 = wstart[q], i1 = wstart[q + 1];
   for (int i = i0; i < i1; ++i) {
     const LdsItem it = items[i];
     const Patch P = patches[it.patch];
     const Walk w = walk_contig(it.tlo, it.thi - it.tlo, it.ntx, it.ntz);
-    split_tiles<ORDER, double, false, false>(P, G, stage, w, L, nullptr);
+    split_tiles<ORDER, double, false, false>(P, G, stage, w, L, nullptr, wave);
     __syncthreads();  // every wave is done with the LDS
   }
 }
@@ -1295,10 +1313,11 @@ __global__ void __launch_bounds__(kSplitThreads)
   __shared__ __attribute__((aligned(16))) SplitLds<ORDER, double> L;
   __shared__ int list[kSplitThreads];
   int* wcnt = (int*)L.mix;  // idle between split_tiles calls
-  const int tid = threadIdx.x;
+  const int wave = wave_id();
   int lo, hi;
   walk_range(blockIdx.x, gridDim.x, ncand, lo, hi);
   for (int c0 = lo; c0 < hi; c0 += kSplitThreads) {
+    const int tid = wave * 64 + lane_id();
     bool f = false;
     if (c0 + tid < hi) {
       const TileRef r = cand[c0 + tid];
@@ -1309,13 +1328,13 @@ __global__ void __launch_bounds__(kSplitThreads)
       tile_origin(r.tile, ntx, ntz, x0, y0, z0);
       f = tile_lapse_min_global(P, x0, y0, z0) < G.alpha_thr;
     }
-    const int n = compact_flags(f, c0 + tid, list, wcnt);
+    const int n = compact_flags(f, c0 + tid, wave, list, wcnt);
     for (int k = 0; k < n; ++k) {
       const TileRef r = cand[list[k]];
       const Patch P = patches[r.patch];
       const OneWalk w{r.tile, (P.n[0] + kLdsTile[0] - 1) / kLdsTile[0],
                       (P.n[2] + kLdsTile[2] - 1) / kLdsTile[2]};
-      split_tiles<ORDER, double, false, false>(P, G, stage, w, L, nullptr);
+      split_tiles<ORDER, double, false, false>(P, G, stage, w, L, nullptr, wave);
       __syncthreads();  // every wave is done with the LDS
     }
     __syncthreads();  // the lists and wcnt are reused
@@ -1445,8 +1464,8 @@ hipError_t launch_stage_lds_periodic(const Patch& P, const Gauge& G, int stage,
 // in x: the boxes' 16-byte granules then wrap as wholes (each lane forms its
 // wrapped DMA offsets once per tile).  Odd ones, and mixed precision (whose
 // tiles are the direct kernels'), stay on the direct kernels.  Measured, direct
-// and here: a 32^3 RK4 step 232 and 108 us, a 96^3 right-hand side 1,330 and
-// 330 us (order 4; 290 with the walk rule of choose_blocks), order 8 3,850 and
+// and here: a 32^3 RK4 step 232 and 102 us, a 96^3 right-hand side 1,330 and
+// 330 us (order 4; 270 with the walk rule of choose_blocks), order 8 3,850 and
 // 513 us.
 inline bool lds_periodic_ok(const Patch& P, int precision) {
   return precision == 0 && P.n[0] % 2 == 0;

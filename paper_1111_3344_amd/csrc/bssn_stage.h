@@ -27,18 +27,30 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const double* base,
                                            kRsrcWord3);
 }
 
-// Buffer resource of slot s built where it is used: the base and the slot
-// stride go through an opaque scalar move, so neither the per-slot
+// Byte offset of slot s (a slot is below 2^31 bytes), formed where it is used.
+__device__ __forceinline__ uint64_t slot_bytes(int64_t sf, int s) {
+  uint32_t o = uint32_t(sf) * 8u;
+  asm volatile("" : "+s"(o));
+  return uint64_t(o) * uint32_t(s);
+}
+// Buffer resource of nbytes at byte offset o of a buffer.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_at(const double* u,
+                                                          uint64_t o,
+                                                          int32_t nbytes) {
+  return rsrc(reinterpret_cast<const double*>(
+                  reinterpret_cast<const char*>(u) + o),
+              nbytes);
+}
+
+// Buffer resource of slot s built where it is used: the slot stride goes
+// through an opaque scalar move, so neither the per-slot
 // descriptors nor the per-slot offsets s*sf of a loop body are hoisted out
 // of the loop (25 slots x 3 buffers x 4 SGPRs, or 25 x 2 SGPRs, would be
 // spilled to VGPR lanes and moved back on every use).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t slot_rsrc(const double* u,
                                                             int64_t sf, int s,
                                                             int32_t nbytes) {
-  const double* b = u;
-  int64_t o = sf;
-  asm volatile("" : "+s"(b), "+s"(o));
-  return rsrc(b + s * o, nbytes);
+  return rsrc_at(u, slot_bytes(sf, s), nbytes);
 }
 
 __device__ __forceinline__ double bload(__amdgpu_buffer_rsrc_t r,
