@@ -41,7 +41,7 @@
 // in each thread (RK4 step, one MI355X): 128^3 order 4 2.91 -> 2.45 ms, 256^3
 // order 4 25.4 -> 19.7 ms, 256^3 order 8 36.4 -> 28.6 ms, 83 x 61 x 45 order 4
 // 531 -> 376 us, 48 uneven patches 18.7 -> 17.1 ms; FP32 at order 8 (mixed
-// precision, 97 x 53 x 75) 1,463 -> 1,112 us.  Prefetching one step ahead
+// precision, 97 x 53 x 75) 1,463 -> 1,076 us.  Prefetching one step ahead
 // instead of two (order 4) cost 8%, updating at the start of a step instead of
 // its end 10%; a branch around the update's loads or stores costs 10-80%, as
 // the compiler then waits for the loads at the branch.
@@ -1188,32 +1188,30 @@ struct OneWalk {
   }
 };
 
-// Minimum lapse over the points of P's tile at (x0, y0, z0), read from
-// global memory by one thread: the value tile_lapse_min takes from the
-// centre block in the FP32 launch (the same points; fmin is exact, so the
-// order does not matter).
-__device__ __forceinline__ double tile_lapse_min_global(const Patch& P,
-                                                        int x0, int y0,
-                                                        int z0) {
-  const int g = P.ghost;
-  const int nx = P.n[0] - x0 < kLdsTile[0] ? P.n[0] - x0 : kLdsTile[0];
-  const int ny = P.n[1] - y0 < kLdsTile[1] ? P.n[1] - y0 : kLdsTile[1];
-  const int nz = P.n[2] - z0 < kLdsTile[2] ? P.n[2] - z0 : kLdsTile[2];
-  const double* a = P.u_s + int64_t(ALP) * P.sf + int64_t(z0 + g) * P.sz +
-                    int64_t(y0 + g) * P.sy + x0 + g;
-  double m = 1.0e300;
-  for (int dz = 0; dz < nz; ++dz)
-    for (int dy = 0; dy < ny; ++dy) {
-      const double* row = a + int64_t(dz) * P.sz + int64_t(dy) * P.sy;
-      if (nx == kLdsTile[0]) {
+// One wave's view of a tile's lapse, four points per lane, read from global
+// memory: whether any point is below thr (a minimum is where a point is: the
+// same points that tile_lapse_min and split_lapse_min see in the FP32 launch).
+struct TileLapse {
+  uint32_t o[4];
+  double a[4];
+  __device__ __forceinline__ void load(const Patch& P, int x0, int y0, int z0,
+                                       int lane) {
+    const __amdgpu_buffer_rsrc_t r =
+        slot_rsrc(P.u_s, P.sf, ALP, int32_t(P.sf * 8));
 #pragma unroll
-        for (int dx = 0; dx < kLdsTile[0]; ++dx) m = fmin(m, row[dx]);
-      } else {
-        for (int dx = 0; dx < nx; ++dx) m = fmin(m, row[dx]);
-      }
+    for (int z = 0; z < 4; ++z) {
+      o[z] = point_offset(P, x0 + (lane & 15), y0 + (lane >> 4), z0 + z);
+      a[z] = bload(r, o[z], 0);
     }
-  return m;
-}
+  }
+  __device__ __forceinline__ bool below(double thr) const {
+    bool f = false;
+#pragma unroll
+    for (int z = 0; z < 4; ++z) f = f || (o[z] != kNoPoint && a[z] < thr);
+    return __builtin_amdgcn_ballot_w64(f) != 0;
+  }
+};
+constexpr int kScan = 8;  // tiles whose loads a wave has in flight
 
 // Writes val of every thread whose flag is set to list, in thread order,
 // and returns their number (the same in every thread).  wcnt: 8 ints of
@@ -1239,7 +1237,10 @@ __device__ __forceinline__ int compact_flags(bool f, int val, int wave,
 
 // One patch, mixed precision, second launch: the FP64 tiles.  Workgroup b
 // examines the tiles t = (i * perm) mod ntiles for i in its share of an
-// even split of 0 .. ntiles - 1, one tile per thread at a time.  perm is
+// even split of 0 .. ntiles - 1, a wave taking kScan tiles at a
+// time (one tile per thread, a serial walk of its 256 points, made the launch
+// 10 us longer: RK4 steps 24^3 263 -> 219 us, 83 x 61 x 45 615 -> 562 us at
+// order 4, 97 x 53 x 75 order 8 1,112 -> 1,076 us; 256^3 equal).  perm is
 // coprime to ntiles, so every tile is examined exactly once, and the tiles
 // around a puncture (neighbours in the numbering) land on many workgroups.
 // The tiles whose minimum lapse is below the threshold run through the FP64
@@ -1259,15 +1260,31 @@ __global__ void __launch_bounds__(kSplitThreads)
   int lo, hi;
   walk_range(blockIdx.x, gridDim.x, M.ntiles, lo, hi);
   for (int c0 = lo; c0 < hi; c0 += kSplitThreads) {
-    const int tid = wave * 64 + lane_id();
-    bool f = false;
-    int t = 0;
-    if (c0 + tid < hi) {
-      t = int((int64_t(c0 + tid) * perm) % M.ntiles);
-      int x0, y0, z0;
-      tile_origin(t, M.ntx, M.ntz, x0, y0, z0);
-      f = tile_lapse_min_global(P, x0, y0, z0) < G.alpha_thr;
+    // lane l of wave w stands for tile c0 + 8 l + w; the wave examines its
+    // lanes' tiles one after the other
+    const int lane = lane_id();
+    const int c = c0 + 8 * lane + wave;
+    const int t = c < hi ? int((int64_t(c) * perm) % M.ntiles) : 0;
+    int x0, y0, z0;
+    tile_origin(t, M.ntx, M.ntz, x0, y0, z0);
+    uint64_t below = 0;
+    const int left = hi - c0 - wave;  // tiles c0 + 8 l + wave < hi
+    const int nl = left <= 0 ? 0 : (left + 7) / 8 < 64 ? (left + 7) / 8 : 64;
+    for (int l0 = 0; l0 < nl; l0 += kScan) {
+      TileLapse v[kScan];
+#pragma unroll
+      for (int i = 0; i < kScan; ++i) {
+        const int l = l0 + i < nl ? l0 + i : l0;
+        v[i].load(P, __builtin_amdgcn_readlane(x0, l),
+                  __builtin_amdgcn_readlane(y0, l),
+                  __builtin_amdgcn_readlane(z0, l), lane);
+      }
+      BSSN_PHASE();
+#pragma unroll
+      for (int i = 0; i < kScan; ++i)
+        below |= uint64_t(l0 + i < nl && v[i].below(G.alpha_thr)) << (l0 + i);
     }
+    const bool f = (below >> lane) & 1;
     const int n = compact_flags(f, t, wave, list, wcnt);
     if (n > 0) {
       const ListWalk w{(const lds_int*)list, n, M.ntx, M.ntz};
@@ -1301,7 +1318,7 @@ __global__ void __launch_bounds__(kSplitThreads)
 
 // Many patches, mixed precision, second launch: the FP64 tiles.  Workgroup
 // b examines the candidates [lo, hi) of an even split of cand (every tile of
-// the launch once, scattered by the plan), one per thread at a time, as
+// the launch once, scattered by the plan) as
 // k_stage_lds_f64tiles does.
 template <int ORDER>
 __global__ void __launch_bounds__(kSplitThreads)
@@ -1317,18 +1334,32 @@ __global__ void __launch_bounds__(kSplitThreads)
   int lo, hi;
   walk_range(blockIdx.x, gridDim.x, ncand, lo, hi);
   for (int c0 = lo; c0 < hi; c0 += kSplitThreads) {
-    const int tid = wave * 64 + lane_id();
-    bool f = false;
-    if (c0 + tid < hi) {
-      const TileRef r = cand[c0 + tid];
-      const Patch& P = patches[r.patch];
-      const int ntx = (P.n[0] + kLdsTile[0] - 1) / kLdsTile[0];
-      const int ntz = (P.n[2] + kLdsTile[2] - 1) / kLdsTile[2];
-      int x0, y0, z0;
-      tile_origin(r.tile, ntx, ntz, x0, y0, z0);
-      f = tile_lapse_min_global(P, x0, y0, z0) < G.alpha_thr;
+    const int lane = lane_id();
+    const int c = c0 + 8 * lane + wave;
+    const TileRef mine = cand[c < hi ? c : lo];
+    uint64_t below = 0;
+    const int left = hi - c0 - wave;
+    const int nl = left <= 0 ? 0 : (left + 7) / 8 < 64 ? (left + 7) / 8 : 64;
+    for (int l0 = 0; l0 < nl; l0 += kScan) {
+      TileLapse v[kScan];
+#pragma unroll
+      for (int i = 0; i < kScan; ++i) {
+        const int l = l0 + i < nl ? l0 + i : l0;
+        const Patch& P = patches[__builtin_amdgcn_readlane(mine.patch, l)];
+        const int ntx = (P.n[0] + kLdsTile[0] - 1) / kLdsTile[0];
+        const int ntz = (P.n[2] + kLdsTile[2] - 1) / kLdsTile[2];
+        int x0, y0, z0;
+        tile_origin(__builtin_amdgcn_readlane(mine.tile, l), ntx, ntz, x0, y0,
+                    z0);
+        v[i].load(P, x0, y0, z0, lane);
+      }
+      BSSN_PHASE();
+#pragma unroll
+      for (int i = 0; i < kScan; ++i)
+        below |= uint64_t(l0 + i < nl && v[i].below(G.alpha_thr)) << (l0 + i);
     }
-    const int n = compact_flags(f, c0 + tid, wave, list, wcnt);
+    const bool f = (below >> lane) & 1;
+    const int n = compact_flags(f, c, wave, list, wcnt);
     for (int k = 0; k < n; ++k) {
       const TileRef r = cand[list[k]];
       const Patch P = patches[r.patch];
