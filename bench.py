@@ -423,7 +423,7 @@ def time_multipole(B, torch, g, reps=10):
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / reps
     del u, work, coeffs
-    return {"kernels": "k_gl_nodes, k_sphere_interp, k_multipole, "
+    return {"kernels": "k_sphere_interp, k_multipole, "
                        "k_multipole_sum",
             "ms_per_call": round(ms, 4), "sphere_points": nt * nph,
             "lmax": lmax, "spin": -2, "radius": radius}
@@ -585,9 +585,9 @@ def summarize_profile(dirs, order=4):
     import collections
     import re
     out = []
-    # the production instantiations (the second template argument, false,
-    # is the radiative-boundary variant's switch)
-    tail = r"\s*(,\s*false\s*)?>\("
+    # the production instantiations (the further template arguments, false,
+    # switch the radiative-boundary and periodic variants)
+    tail = r"\s*(,\s*false\s*)*>\("
     kernels = (("", re.compile(r"k_stage_lds<\s*%d" % order + tail)),
                ("mixed_f32_", re.compile(r"k_stage_lds_f32<\s*%d" % order +
                                          tail)),

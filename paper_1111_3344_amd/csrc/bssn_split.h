@@ -3,11 +3,11 @@
 // A workgroup of 512 threads owns one 16 x 4 x 4 tile at a time.  Each point
 // belongs to two threads, whose registers (256 each) share its working set:
 //   * the curvature waves (0..3, wave w = plane w of the tile) form the
-//     derivatives and the pointwise algebra;
+//     derivatives and the pointwise algebra, and issue the buffer->LDS DMA of
+//     the stencil boxes;
 //   * the transport waves (4..7) form the advection + dissipation sum of
-//     every slot, run the RK4 update, and move all memory: they issue the
-//     buffer->LDS DMA of the stencil boxes and the loads and stores of u_n,
-//     acc and the stage output.
+//     every slot and run the RK4 update: the loads and stores of u_n, acc and
+//     the stage output.
 // One wave per SIMD (a whole point per thread needs more than 256 registers)
 // leaves the issue slots of every LDS round trip, dependent FP64 result and
 // memory wait empty; the second wave fills them.
@@ -32,9 +32,10 @@
 // over the whole tile time instead of meeting in one burst.
 //
 // What bounds it: the two waves of a SIMD are close to balanced and both
-// latency-bound (an order-4 tile takes about 43,000 cycles, of which the
-// curvature waves wait 7,000 and the transport waves 4,000); the DMA takes
-// about 15,000 cycles of the CU's address unit, and its issue blocks the wave
+// latency-bound (an order-4 tile takes about 41,000 cycles: the SIMDs issue
+// vector instructions in 46% of them and scalar ones in 22%, the LDS is busy in
+// 43%, a wave spends 39% in waits and barriers); the DMA takes about 15,000
+// cycles of the CU's address unit, and its issue blocks the wave
 // for 100-150 cycles per instruction, so it sits in the curvature waves,
 // whose arithmetic is the shorter, right after the barrier that the inner
 // sums need anyway.  Measured against one wave per SIMD with the whole point
@@ -77,7 +78,7 @@ struct SplitGeo {
   static constexpr int W = (TX + 2 * R + 3) / 2 * 2;  // even, one pad column
   static constexpr int H = TY + 2 * R, D = TZ + 2 * R;
   // heavy box: G granules of 16 bytes, NI DMA instructions of 64 lanes, at
-  // most L per transport wave
+  // most L per curvature wave
   static constexpr int G = W * H * D / 2, NI = (G + 63) / 64,
                        L = (NI + 3) / 4, BUFD = NI * 128;
   // light slot: x, y and z runs
