@@ -45,12 +45,12 @@ struct Gauge {
   double alpha_thr;
 };
 
-// Work items of the batched kernels.  LDS kernel: a run of tiles [tlo, thi)
-// of one patch whose tile grid is ntx x nty x ntz (tiles numbered z fastest
-// within an (x, y) column).  Direct kernel: the workgroup-shaped tile at
+// Work items of the batched kernels.  LDS kernel: every stride-th tile of
+// [tlo, thi) of one patch whose tile grid is ntx wide and ntz deep (tiles
+// numbered z fastest within an (x, y) column).  Direct kernel: the workgroup-shaped tile at
 // (x0, y0) of a z-block of planes of one patch.
 struct LdsItem {
-  int32_t patch, tlo, thi, ntx, nty, ntz;
+  int32_t patch, tlo, thi, stride, ntx, ntz;
 };
 struct DirectItem {
   int32_t patch, x0, y0, z0;  // planes z0 .. z0 + depth - 1

@@ -41,7 +41,7 @@
 // sums need anyway.  Measured against one wave per SIMD with the whole point
 // in each thread (RK4 step, one MI355X): 128^3 order 4 2.91 -> 2.45 ms, 256^3
 // order 4 25.4 -> 19.7 ms, 256^3 order 8 36.4 -> 28.6 ms, 83 x 61 x 45 order 4
-// 531 -> 376 us, 48 uneven patches 18.7 -> 17.1 ms; FP32 at order 8 (mixed
+// 531 -> 376 us, 48 uneven patches 18.7 -> 17.1 ms (14.8 with dealt tiles); FP32 at order 8 (mixed
 // precision, 97 x 53 x 75) 1,463 -> 1,076 us.  Prefetching one step ahead
 // instead of two (order 4) cost 8%, updating at the start of a step instead of
 // its end 10%; a branch around the update's loads or stores costs 10-80%, as
@@ -532,7 +532,8 @@ __device__ __forceinline__ void curvature_waves(const Patch& P, const Gauge& G,
   using Geo = SplitGeo<ORDER>;
   typedef __attribute__((address_space(3))) T lds_t;
   const int n = Wk.count();
-  const int32_t nbytes = int32_t(P.sf * 8);
+  // (scalar, as in Transport)
+  const int32_t nbytes = __builtin_amdgcn_readfirstlane(int32_t(P.sf * 8));
   T ih[3], ih2[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
@@ -1138,6 +1139,11 @@ __global__ void __launch_bounds__(kF32Threads<ORDER>)
   f32_tiles<ORDER, KSH>(P, G, stage, walk_of(M, gridDim.x), L, kout);
 }
 
+// The tiles of a work item.
+__device__ __forceinline__ int item_tiles(const LdsItem& it) {
+  return (it.thi - it.tlo + it.stride - 1) / it.stride;
+}
+
 // Many patches, mixed precision, first launch: the FP32 tiles, with split
 // (1 or 2) workgroups per work list position.  Workgroup b' stands for
 // workgroup b of the list's launch of nwg on the same XCD (b' mod 8 = b mod
@@ -1159,9 +1165,10 @@ __global__ void __launch_bounds__(kF32Threads<ORDER>)
   for (int i = i0; i < i1; ++i) {
     const LdsItem it = items[i];
     const Patch P = patches[it.patch];
-    const int n = it.thi - it.tlo;
-    const int lo = it.tlo + n * h / split, hi = it.tlo + n * (h + 1) / split;
-    const Walk w = walk_contig(lo, hi - lo, it.ntx, it.ntz);
+    const int n = item_tiles(it);
+    const int lo = n * h / split, hi = n * (h + 1) / split;
+    const Walk w = walk_dealt(it.tlo + lo * it.stride, hi - lo, it.stride,
+                              it.ntx, it.ntz);
     f32_tiles<ORDER, false>(P, G, stage, w, L, nullptr);
     __syncthreads();  // every wave is done with the LDS
   }
@@ -1311,7 +1318,8 @@ __global__ void __launch_bounds__(kSplitThreads)
   for (int i = i0; i < i1; ++i) {
     const LdsItem it = items[i];
     const Patch P = patches[it.patch];
-    const Walk w = walk_contig(it.tlo, it.thi - it.tlo, it.ntx, it.ntz);
+    const Walk w =
+        walk_dealt(it.tlo, item_tiles(it), it.stride, it.ntx, it.ntz);
     split_tiles<ORDER, double, false, false>(P, G, stage, w, L, nullptr, wave);
     __syncthreads();  // every wave is done with the LDS
   }
@@ -1388,9 +1396,10 @@ inline TileMap lds_tile_map(const Patch& P) {
 // Blocked walk (Walk with bx > 0) for a launch of 256 or 512 workgroups
 // (one or two per CU): the first block shape of nwg / 8 tiles that divides
 // the tile grid and gives no workgroup more than 5% more tiles than the even
-// split of the contiguous walk does (the blocks' cache sharing is worth 3-10%;
-// 18 block columns on 8 XCDs, a 96^3 grid, would cost 29%: 330 against
-// 290 us per order-4 right-hand side); otherwise the contiguous walk.  Order 8
+// split of the dealt walk does (18 block columns on 8 XCDs, a 96^3 grid, would
+// cost 29%: 330 against 266 us per order-4 right-hand side; blocks share
+// halos in three directions, dealt tiles in z and partly in y and x);
+// otherwise the dealt walk.  Order 8
 // (a 14-plane box) measured best with blocks 2 tiles deep in z, order 4 with 4.
 template <int ORDER>
 inline void choose_blocks(TileMap& M, int nwg) {
@@ -1497,7 +1506,7 @@ hipError_t launch_stage_lds_periodic(const Patch& P, const Gauge& G, int stage,
 // wrapped DMA offsets once per tile).  Odd ones, and mixed precision (whose
 // tiles are the direct kernels'), stay on the direct kernels.  Measured, direct
 // and here: a 32^3 RK4 step 232 and 102 us, a 96^3 right-hand side 1,330 and
-// 330 us (order 4; 270 with the walk rule of choose_blocks), order 8 3,850 and
+// 330 us (order 4; 266 with the walks as they are now), order 8 3,850 and
 // 513 us.
 inline bool lds_periodic_ok(const Patch& P, int precision) {
   return precision == 0 && P.n[0] % 2 == 0;
