@@ -1197,8 +1197,12 @@ struct OneWalk {
 };
 
 // One wave's view of a tile's lapse, four points per lane, read from global
-// memory: whether any point is below thr (a minimum is where a point is: the
-// same points that tile_lapse_min and split_lapse_min see in the FP32 launch).
+// memory: whether any point is below thr.  Each point counts as
+// fmin(1e300, lapse), as in the minimum that tile_lapse_min and
+// split_lapse_min compare in the FP32 launch: a tile whose lapse is NaN (or
+// above 1e300) at every point has the value 1e300 in both launches, so that with
+// a threshold above that (+inf: everything in FP64) exactly one of them takes
+// it.
 struct TileLapse {
   uint32_t o[4];
   double a[4];
@@ -1215,7 +1219,8 @@ struct TileLapse {
   __device__ __forceinline__ bool below(double thr) const {
     bool f = false;
 #pragma unroll
-    for (int z = 0; z < 4; ++z) f = f || (o[z] != kNoPoint && a[z] < thr);
+    for (int z = 0; z < 4; ++z)
+      f = f || (o[z] != kNoPoint && fmin(1.0e300, a[z]) < thr);
     return __builtin_amdgcn_ballot_w64(f) != 0;
   }
 };
