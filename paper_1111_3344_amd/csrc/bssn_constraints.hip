@@ -38,10 +38,15 @@ __device__ __forceinline__ void grad(const L& ld, int s, const double (&ih)[3],
   }
 }
 
-// Mixed second derivative (the sums of mixed()), with a compiler fence per
-// row of the stencil: it keeps the row's reads inside the row instead of
-// hoisting all of them, which spills registers.
-template <int ORDER, class L>
+// FENCE, here and below: the kernel that reads LDS.  There a compiler fence per
+// row of the stencil keeps the row's reads inside the row instead of hoisting all
+// of them, which spills registers.  The direct kernels run without: the more
+// of their global loads are in flight the better (with the fences a periodic
+// 128^3 call takes 923 us at order 4 and 3,580 at order 8, without 599 and
+// 2,630).
+
+// Mixed second derivative (the sums of mixed()).
+template <int ORDER, bool FENCE, class L>
 __device__ __forceinline__ double mixed_rows(const L& ld, int s, int a, int b,
                                              double ihab) {
   using F = FD<ORDER>;
@@ -55,13 +60,13 @@ __device__ __forceinline__ double mixed_rows(const L& ld, int s, int a, int b,
       m += F::a(j) * (ld.pl(s, a, -i, b, j) - ld.pl(s, a, -i, b, -j));
     }
     acc += F::a(i) * (p - m);
-    asm volatile("" : "+v"(acc)::"memory");
+    if constexpr (FENCE) asm volatile("" : "+v"(acc)::"memory");
   }
   return acc * ihab;
 }
 
 // full symmetric Hessian (S-indexed)
-template <int ORDER, class L>
+template <int ORDER, bool FENCE, class L>
 __device__ __forceinline__ void hess(const L& ld, int s, const double (&ih)[3],
                                      double (&dd)[6]) {
   using F = FD<ORDER>;
@@ -72,12 +77,12 @@ __device__ __forceinline__ void hess(const L& ld, int s, const double (&ih)[3],
 #pragma unroll
     for (int k = 1; k <= F::M; ++k)
       s2 += F::b(k) * ((ld.ax(s, a, k) - c0) + (ld.ax(s, a, -k) - c0));
-    asm volatile("" : "+v"(s2)::"memory");
+    if constexpr (FENCE) asm volatile("" : "+v"(s2)::"memory");
     dd[S(a, a)] = s2 * ih[a] * ih[a];
   }
-  dd[1] = mixed_rows<ORDER>(ld, s, 0, 1, ih[0] * ih[1]);
-  dd[2] = mixed_rows<ORDER>(ld, s, 0, 2, ih[0] * ih[2]);
-  dd[4] = mixed_rows<ORDER>(ld, s, 1, 2, ih[1] * ih[2]);
+  dd[1] = mixed_rows<ORDER, FENCE>(ld, s, 0, 1, ih[0] * ih[1]);
+  dd[2] = mixed_rows<ORDER, FENCE>(ld, s, 0, 2, ih[0] * ih[2]);
+  dd[4] = mixed_rows<ORDER, FENCE>(ld, s, 1, 2, ih[1] * ih[2]);
 }
 
 // H, M_i and G^i at one point.  The loader's enter(s) opens the phase of slot
@@ -95,7 +100,7 @@ __host__ __device__ constexpr int con_phase(int s) {
                                   : 11 + s - AXX;
 }
 
-template <int ORDER, class L>
+template <int ORDER, bool FENCE, class L>
 __device__ __forceinline__ void constraints_point(const L& ld,
                                                   const double (&ih)[3],
                                                   double& H, double (&M)[3],
@@ -110,7 +115,7 @@ __device__ __forceinline__ void constraints_point(const L& ld,
     ld.enter(GXX + m);
     grad<ORDER>(ld, GXX + m, ih, dgt[m]);
     double dd[6];
-    hess<ORDER>(ld, GXX + m, ih, dd);
+    hess<ORDER, FENCE>(ld, GXX + m, ih, dd);
     Rt[m] = -0.5 * (gu[0] * dd[0] + gu[3] * dd[3] + gu[5] * dd[5] +
                     2.0 * (gu[1] * dd[1] + gu[2] * dd[2] + gu[4] * dd[4]));
     keep(Rt[m]);
@@ -118,7 +123,7 @@ __device__ __forceinline__ void constraints_point(const L& ld,
     for (int a = 0; a < 3; ++a) keep(dgt[m][a]);
   }
   double Gu[3][6], Gd[3];
-  connection<double, true>(dgt, gu, Gu, Gd, Rt);
+  connection<double, FENCE>(dgt, gu, Gu, Gd, Rt);
   double Gt[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
@@ -143,7 +148,7 @@ __device__ __forceinline__ void constraints_point(const L& ld,
   ld.enter(PHI);
   const double phi = ld.c(PHI);
   grad<ORDER>(ld, PHI, ih, dphi);
-  hess<ORDER>(ld, PHI, ih, ddphi);
+  hess<ORDER, FENCE>(ld, PHI, ih, ddphi);
   double trDD = 0.0, dphi2 = 0.0;
 #pragma unroll
   for (int m = 0; m < 6; ++m) {
@@ -318,7 +323,7 @@ __global__ void __launch_bounds__(256)
       ld.str[0] = 8u;
       ld.str[1] = sy8;
       ld.str[2] = sz8;
-      constraints_point<ORDER>(ld, ih, H, M, Gc);
+      constraints_point<ORDER, false>(ld, ih, H, M, Gc);
     } else {
       LdPeriodic<R> ld;
       ld.u = A.u;
@@ -334,7 +339,7 @@ __global__ void __launch_bounds__(256)
           q = q < 0 ? q + A.n[a] : (q >= A.n[a] ? q - A.n[a] : q);
           ld.o[a][R + k] = uint32_t(q + g) * st[a];
         }
-      constraints_point<ORDER>(ld, ih, H, M, Gc);
+      constraints_point<ORDER, false>(ld, ih, H, M, Gc);
     }
     point_result(A, x, y, z, vc, nbytes, H, M, Gc, v);
   }
@@ -352,9 +357,9 @@ __global__ void __launch_bounds__(256)
 // LDS buffers by buffer->LDS DMA, NB - 1 phases ahead.  What bounded the
 // direct kernel was its 500 to 1,500 global loads per point; here a tap is an
 // LDS read and each box is fetched once per tile.  A 128^3 call with fields and
-// norms takes 331 us at order 4 instead of 784 (it moves 403 MB, so 1.2 TB/s);
-// what is left is the latency of the LDS reads and the algebra at two waves
-// per SIMD.
+// norms takes 331 us at order 4 (it moves 403 MB, so 1.2 TB/s), 604 in the
+// direct kernel; what is left is the latency of the LDS reads and the algebra
+// at two waves per SIMD.
 template <int ORDER>
 struct ConGeo {
   static constexpr int M = FD<ORDER>::M, TX = kLdsTile[0], TY = kLdsTile[1],
@@ -505,7 +510,7 @@ __global__ void __launch_bounds__(256)
     vm_wait_n<(Geo::NB - 1) * (Geo::NI - 3 * Geo::L)>();
   __builtin_amdgcn_s_barrier();
   double H, M[3], Gc[3];
-  constraints_point<ORDER>(ld, ih, H, M, Gc);
+  constraints_point<ORDER, true>(ld, ih, H, M, Gc);
   double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   if (x < A.n[0] && y < A.n[1] && z < A.n[2]) {
     const uint32_t vc =
