@@ -18,3 +18,10 @@ def test_order4_constraints_fit_two_waves_per_simd(kernels):
         # vgpr_count counts the accumulation registers too
         assert v["vgpr_count"] <= 256, k
         assert not v["private_segment_fixed_size"], k
+
+
+def test_order8_periodic_fp32_stage_spills_little(kernels):
+    # one thread per point does not fit 512 registers here: at most 8 of them
+    # in scratch
+    (v,) = _select(kernels, r"7k_stageILi8ELb1ELi1E").values()
+    assert v["private_segment_fixed_size"] <= 32
