@@ -3,9 +3,10 @@
 // multipole module projects a field interpolated onto spheres onto
 // spin-weighted spherical harmonics, C^lm = integral conj(sY_lm) u r^2 dOmega).
 //
-// Three launches:
+// Three launches, four for large spheres:
+//   k_gl_nodes      (large spheres) the Gauss-Legendre nodes theta_j;
 //   k_sphere_interp four threads per sphere point (theta_j, phi_k): the
-//                   Gauss-Legendre node theta_j, and the tricubic
+//                   node theta_j where it is not there yet, and the tricubic
 //                   interpolation of the real and imaginary parts (4 x 4 x 4
 //                   storage points, block clamped into the grid);
 //   k_multipole     one workgroup per (l, m, chunk of the points): the sum
@@ -90,25 +91,49 @@ __device__ __forceinline__ void gl_node(const double2* rec, int n, int j,
   w = 2.0 / ((1.0 - z * z) * dp * dp);
 }
 
+// The recurrence's ratios up to n, by the nt threads of a workgroup.
+__device__ __forceinline__ void fill_ratios(double2* rec, int n, int nt) {
+  for (int k = 2 + threadIdx.x; k <= n; k += nt)
+    rec[k] = {(2.0 * k - 1.0) / k, (k - 1.0) / k};
+  __syncthreads();
+}
+
+// The nodes by themselves, one per thread.
+__global__ void __launch_bounds__(64)
+    k_gl_nodes(const int n, double* __restrict__ xs, double* __restrict__ ws) {
+  extern __shared__ double2 rec[];
+  fill_ratios(rec, n, 64);
+  const int j = blockIdx.x * 64 + threadIdx.x;
+  if (j >= n) return;
+  double x, w;
+  gl_node(rec, n, j, x, w);
+  xs[j] = x;
+  ws[j] = w;
+}
+
 // Lane q of a point's four takes the z plane q of its 4 x 4 x 4 block, so its
-// 32 loads are in flight together.  Each point works out its own node (one
-// Newton iteration per wave either way); the first of a row leaves it for the
-// next launch.
+// 32 loads are in flight together.  NODES: each point works out its own node
+// and the first of a row leaves it for the next launch; else the nodes are
+// there (launch_multipole has the rule).
+template <bool NODES>
 __global__ void __launch_bounds__(256)
     k_sphere_interp(const MultipoleArgs A, double* __restrict__ xs,
                     double* __restrict__ ws, double* __restrict__ val) {
   extern __shared__ double2 rec[];
-  for (int k = 2 + threadIdx.x; k <= A.ntheta; k += 256)
-    rec[k] = {(2.0 * k - 1.0) / k, (k - 1.0) / k};
-  __syncthreads();
+  if constexpr (NODES) fill_ratios(rec, A.ntheta, 256);
   const int p = (blockIdx.x * 256 + threadIdx.x) >> 2, kk = threadIdx.x & 3;
   if (p >= A.ntheta * A.nphi) return;
   const int j = p / A.nphi, k = p % A.nphi;
-  double ct, wj;
-  gl_node(rec, A.ntheta, j, ct, wj);
-  if (k == 0 && kk == 0) {
-    xs[j] = ct;
-    ws[j] = wj;
+  double ct;
+  if constexpr (NODES) {
+    double wj;
+    gl_node(rec, A.ntheta, j, ct, wj);
+    if (k == 0 && kk == 0) {
+      xs[j] = ct;
+      ws[j] = wj;
+    }
+  } else {
+    ct = xs[j];
   }
   const double st = sqrt(fmax(0.0, 1.0 - ct * ct));
   const double ph = 2.0 * M_PI * k / A.nphi;
@@ -250,6 +275,17 @@ __global__ void __launch_bounds__(64)
   coeffs[2 * q + 1] = im * radius * radius;
 }
 
+// Whether each sphere point works out its own node (no launch more).  That takes
+// one Newton iteration per wave, as long as one iteration in a launch of its own
+// while the waves of a SIMD fill each other's waits; beyond two per SIMD (32,768
+// points) they queue, and the redundant recurrence steps, points x ntheta of them
+// per iteration, come to cost more than a launch does.  Both ways, own nodes first
+// (us per call, l <= 8): 64 x 128 26 and 27, 512 x 64 83 and 87, 180 x 266 66 and
+// 67, 360 x 100 79 and 76, 256 x 512 152 and 129, 1024 x 128 343 and 198,
+// 1024 x 4096 9,040 and 2,760.
+inline bool own_nodes(int ntheta, int npts) {
+  return npts <= 32768 || int64_t(npts) * ntheta <= 1 << 23;
+}
 }  // namespace
 
 hipError_t launch_multipole(const MultipoleArgs& A, double* work,
@@ -258,9 +294,21 @@ hipError_t launch_multipole(const MultipoleArgs& A, double* work,
   double* w = work + A.ntheta;
   double* val = work + 2 * A.ntheta;
   const int npts = A.ntheta * A.nphi;
-  hipLaunchKernelGGL(k_sphere_interp, dim3((npts + 63) / 64), dim3(256),
-                     sizeof(double2) * (A.ntheta + 1), st, A, x, w, val);
-  hipError_t e = hipGetLastError();
+  const size_t ratios = sizeof(double2) * (A.ntheta + 1);
+  const dim3 grd((npts + 63) / 64);
+  hipError_t e;
+  if (own_nodes(A.ntheta, npts)) {
+    hipLaunchKernelGGL(k_sphere_interp<true>, grd, dim3(256), ratios, st, A, x,
+                       w, val);
+  } else {
+    hipLaunchKernelGGL(k_gl_nodes, dim3((A.ntheta + 63) / 64), dim3(64),
+                       ratios, st, A.ntheta, x, w);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_sphere_interp<false>, grd, dim3(256), 0, st, A, x, w,
+                       val);
+  }
+  e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int nq = (A.lmax + 1) * (A.lmax + 1);
   // four points per thread repay forming the coefficients; never more chunks
