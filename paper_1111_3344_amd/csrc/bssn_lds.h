@@ -468,7 +468,7 @@ __device__ __forceinline__ Walk walk_dealt(int tlo, int n, int stride,
 // holds all 256 of them) in every wave, so that each wave reaches the same
 // value without a barrier.  Points outside the grid do not count.  fmin is
 // exact, so the value does not depend on the order of reduction; the FP64
-// pass compares the same values from global memory, point by point (TileLapse).
+// pass takes the same decision from global memory, point by point (TileLapse).
 __device__ __forceinline__ double tile_lapse_min(const double* sc,
                                                  const Patch& P, int x, int y,
                                                  int z0, int lane) {

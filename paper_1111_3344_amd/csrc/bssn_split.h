@@ -1201,12 +1201,7 @@ struct OneWalk {
 };
 
 // One wave's view of a tile's lapse, four points per lane, read from global
-// memory: whether any point is below thr.  Each point counts as
-// fmin(1e300, lapse), as in the minimum that tile_lapse_min and
-// split_lapse_min compare in the FP32 launch: a tile whose lapse is NaN (or
-// above 1e300) at every point has the value 1e300 in both launches, so that with
-// a threshold above that (+inf: everything in FP64) exactly one of them takes
-// it.
+// memory: whether any point is below thr.
 struct TileLapse {
   uint32_t o[4];
   double a[4];
@@ -1223,12 +1218,22 @@ struct TileLapse {
   __device__ __forceinline__ bool below(double thr) const {
     bool f = false;
 #pragma unroll
-    for (int z = 0; z < 4; ++z)
-      f = f || (o[z] != kNoPoint && fmin(1.0e300, a[z]) < thr);
+    for (int z = 0; z < 4; ++z) f = f || (o[z] != kNoPoint && a[z] < thr);
     return __builtin_amdgcn_ballot_w64(f) != 0;
   }
 };
 constexpr int kScan = 8;  // tiles whose loads a wave has in flight
+
+// Whether the FP64 pass takes tile c of its share (c < hi), below: whether a
+// point of it is below thr.  The FP32 launch leaves out the tiles for which the
+// minimum of tile_lapse_min and split_lapse_min is below thr.  That minimum
+// starts at 1e300 and leaves NaN out: it is below thr where a point is, and
+// everywhere if thr exceeds 1e300 (+inf: everything in FP64), also where the lapse
+// is NaN at every point.
+__device__ __forceinline__ bool fp64_tile(bool below, double thr, int c,
+                                          int hi) {
+  return below || (thr > 1.0e300 && c < hi);
+}
 
 // Writes val of every thread whose flag is set to list, in thread order,
 // and returns their number (the same in every thread).  wcnt: 8 ints of
@@ -1301,7 +1306,7 @@ __global__ void __launch_bounds__(kSplitThreads)
       for (int i = 0; i < kScan; ++i)
         below |= uint64_t(l0 + i < nl && v[i].below(G.alpha_thr)) << (l0 + i);
     }
-    const bool f = (below >> lane) & 1;
+    const bool f = fp64_tile((below >> lane) & 1, G.alpha_thr, c, hi);
     const int n = compact_flags(f, t, wave, list, wcnt);
     if (n > 0) {
       const ListWalk w{(const lds_int*)list, n, M.ntx, M.ntz};
@@ -1376,7 +1381,7 @@ __global__ void __launch_bounds__(kSplitThreads)
       for (int i = 0; i < kScan; ++i)
         below |= uint64_t(l0 + i < nl && v[i].below(G.alpha_thr)) << (l0 + i);
     }
-    const bool f = (below >> lane) & 1;
+    const bool f = fp64_tile((below >> lane) & 1, G.alpha_thr, c, hi);
     const int n = compact_flags(f, c, wave, list, wcnt);
     for (int k = 0; k < n; ++k) {
       const TileRef r = cand[list[k]];
