@@ -110,10 +110,12 @@ int bssn_abi_version(void);
 /* Kernel selection for bssn_rhs / rk4_stage (process-wide; results agree to
  * rounding, both are checked against the same reference):
  *   BSSN_PATH_AUTO    persistent kernel that stages every slot's stencil box
- *                     in LDS through buffer->LDS DMA, for static grids whose
- *                     layout gives 16-byte aligned rows (even strides and
- *                     ptr + ghost - R - 1 aligned, R = 3 or 5); the
- *                     direct-load kernel otherwise;
+ *                     in LDS through buffer->LDS DMA, for layouts that give
+ *                     16-byte aligned rows (even strides and
+ *                     ptr + ghost - R - 1 aligned, R = 3 or 5) of static
+ *                     grids and, in FP64, of periodic grids with n[0] even;
+ *                     the direct-load kernel otherwise (odd periodic n[0],
+ *                     periodic grids in mixed precision, other layouts);
  *   BSSN_PATH_DIRECT  always the direct-load kernel (one thread per point,
  *                     stencil taps read through the caches).
  * Errors: BSSN_EINVAL for other values. */
@@ -243,8 +245,10 @@ int bssn_track_punctures(const bssn_grid* grid, const double* u, int npunct,
  *           / 256)) doubles
  *   coeffs  device, 2 (lmax + 1)^2 doubles: (re, im) of C^{lm} at index
  *           l*l + l + m; zero for l < |spin|
- * Four launches on `stream`; the sums run in a fixed order (the result is
- * deterministic).  Errors: BSSN_EINVAL, BSSN_EUNSUPPORTED, BSSN_EHIP. */
+ * Three launches on `stream`, four for large spheres (more than 32,768 points
+ * and more than 2^23 of ntheta^2 nphi); the sums run in a fixed order (the
+ * result is deterministic).  Errors: BSSN_EINVAL, BSSN_EUNSUPPORTED,
+ * BSSN_EHIP. */
 int bssn_multipole(const bssn_grid* grid, const double* re, const double* im,
                    const double* centre, double radius, int spin, int lmax,
                    int ntheta, int nphi, double* work, double* coeffs,

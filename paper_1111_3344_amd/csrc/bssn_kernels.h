@@ -13,8 +13,9 @@ namespace bssn {
 // stored by the LDS kernels from their own tiles, or by the shell kernel
 // (FP64) before a direct-kernel stage.
 // Kernel choice: PATH_AUTO uses the LDS-pipelined persistent kernel for
-// static grids whose layout allows 16-byte granules, the direct-load kernel
-// otherwise; PATH_DIRECT forces the direct-load kernel.
+// layouts that allow 16-byte granules, on static grids and, in FP64, periodic
+// ones with an even number of points in x; the direct-load kernel otherwise.
+// PATH_DIRECT forces the direct-load kernel.
 enum : int { PATH_AUTO = 0, PATH_DIRECT = 1 };
 hipError_t launch_stage_o4(const Patch& P, const Gauge& G, int periodic,
                            int stage, int precision, int path, int nwg,

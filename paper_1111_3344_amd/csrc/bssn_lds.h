@@ -31,8 +31,8 @@
 // finds those tiles by the same test and runs them in FP64.
 //
 // Tiles are walked persistently (Walk): in blocks of 32 (or 64) tiles per
-// XCD stepping together in z where the tile grid allows, else in contiguous
-// z-column runs, so tiles whose halos overlap are in flight on one XCD and
+// XCD stepping together in z where the tile grid allows, else dealt in turn to
+// an XCD's workgroups, so tiles whose halos overlap are in flight on one XCD and
 // meet in its L2.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -69,7 +69,6 @@ struct MixGeo {
   static constexpr int NZ = 2 * M * Geo::TY * Geo::TX;
   static constexpr int NE = 2 * NX + NZ;
   static constexpr int NC = NE / 64;          // chunks
-  static constexpr int NR = (NC + 3) / 4;     // chunks per wave (at most)
   static_assert(NX % 64 == 0 && NZ % 64 == 0, "whole chunks per part");
 };
 
@@ -229,7 +228,7 @@ constexpr int kCentrePhase = 1;
 constexpr int kCentreL = kNCentre * 128 / 256;  // DMA instructions per wave
 
 // Per-lane DMA offsets of the centre block of the tile at (x0, y0, z0):
-// instruction j of wave w moves half of slot kCentreSlots[(9w + j) / 2].
+// instruction j of wave w moves half of slot kCentreSlots[(5w + j) / 2].
 __device__ __forceinline__ void centre_dma(const Patch& P, double* sc,
                                            int x0, int y0, int z0, int wave,
                                            int lane) {

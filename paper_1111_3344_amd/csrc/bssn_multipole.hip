@@ -18,10 +18,11 @@
 //   sin^{2l-k}(theta/2) cos^{k}(theta/2), k = 2r + s - m in [0, 2l],
 // so no cotangent is formed.
 // A sphere is a few thousand points, so every launch is bound by the latency
-// of its serial chains, not by memory.  64 x 128 points with l <= 8: 33 us for
-// the three, against 74 us when the nodes were a launch of their own with a
-// division per recurrence step (22), the interpolation took one thread per
-// point (25) and every point formed its binomials (21).
+// of its serial chains, not by memory.  64 x 128 points with l <= 8: 26 us a
+// call in a row of calls (33 us of kernels in a trace), against 58 (74) when the
+// nodes were a launch of their own with a division per recurrence step (22 in
+// the trace), the interpolation took one thread per point (25) and every point
+// formed its binomials (21).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -192,8 +193,8 @@ __global__ void __launch_bounds__(256)
 
 // With r from r0 to r1 the powers in Goldberg's sum step by cos^2 up and sin^2
 // down, so a point's sum is a homogeneous Horner scheme over coefficients that
-// the workgroup forms once (l <= 16 and |s| <= 8 by the entry point's checks, so
-// there are at most 25).
+// the workgroup forms once (r1 - r0 <= l - max(|m|, |s|) and l <= 16 by the entry
+// point's check, so there are at most 17).
 __global__ void __launch_bounds__(256)
     k_multipole(const MultipoleArgs A, const double* __restrict__ x,
                 const double* __restrict__ w, const double* __restrict__ val,
